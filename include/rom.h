@@ -80,7 +80,9 @@ extern "C" {
 /* Sweep kernels.  STRIP: ordinates on lanes, strips of cells handed from wavefront to wavefront
  * (every scheme, source kind and angular-flux output).  DIAG: grid rows on lanes, each
  * wavefront sweeping the anti-diagonals of a 16- or 64-row block with the y-face value passed one
- * lane up; far more parallel work per ordinate, for isotropic step-scheme source iteration. */
+ * lane up; far more parallel work per ordinate, for isotropic step-scheme source iteration.  With
+ * AUTO librom may also take a third kernel, which sweeps whole rows as prefix scans (isotropic step
+ * sources, nx <= 1024); it reports itself as ROM_SWEEP_DIAG with lanes = 1. */
 #define ROM_SWEEP_AUTO 0
 #define ROM_SWEEP_STRIP 1
 #define ROM_SWEEP_DIAG 2
@@ -139,13 +141,15 @@ typedef struct {
     int64_t updates;       /* cell x ordinate upwind updates performed */
     double device_ms;      /* device time of the solve, from events on the handle's stream */
     double sweep_ms;       /* summed duration of the sweep launches that did work, from the end of
-                              the kernel before each (its dispatch) to its last wave's end, on the
-                              device real-time clock */
+                              the kernel before each (its dispatch) to its last wave's end (to the
+                              next kernel's start for row-scan sweeps), on the device real-time
+                              clock */
     int32_t sweeps;        /* sweep launches that did work */
     int32_t tile_x, tile_y;/* strip sweep: chunk x strip shape; row-lane sweep: ordinates per lane
                               and rows per lane block (set or autotuned) */
     int32_t band;          /* strips (strip sweep) or wavefronts (row-lane sweep) per workgroup */
-    int32_t lanes;         /* strip sweep: lanes per ordinate group (16, 32 or 64) */
+    int32_t lanes;         /* strip sweep: lanes per ordinate group (16, 32 or 64); row-lane sweep: rows
+                              per lane block; row-scan sweep: 1 */
     int32_t sweep;         /* ROM_SWEEP_STRIP or ROM_SWEEP_DIAG */
 } rom_si_stats;
 

@@ -198,6 +198,12 @@ int spin_limit()
 struct Plan;
 struct Arena;
 
+// The row-scan sweep, chosen by librom only (rom_si_opts asks for the strip or row-lane kernel, or
+// leaves the choice).  Its shape travels in the options' fields of the other sweeps: band =
+// wavefronts W; diag_rows = lanes per row G and tile_x = cells per lane C of the single-ordinate
+// form (W = kScanWaves).
+constexpr int kSweepScan = 3;
+
 struct rom_handle {
     rom_grid grid{};
     double dx = 0, dy = 0;
@@ -329,6 +335,11 @@ struct Plan {
     int dR = 16, dK = 1, dNB = 1;
     std::vector<DiagTaskDev> dtasks;
     DevMem d_dtasks;
+    // row-scan sweep
+    int sG = 64, sC = 4, sW = kScanWaves;
+    std::vector<ScanTaskDev> stasks;
+    DevMem d_stasks;
+    int64_t pad = kPoolPad;  // elements of padding on both sides of the sigma_t and source pools
 
     DevMem d_probs, d_sys, d_ws, d_lanes, d_tickets, d_slot_off, d_slot_order, d_slot_off_ord, d_cblocks;
     DevMem d_st, d_ss, d_q, d_src, d_phi, d_part, d_edge, d_inflow, d_prog, d_ctl, d_sysctl, d_rhist;
@@ -364,9 +375,36 @@ struct Plan {
         if (ev1) (void)hipEventDestroy(ev1);
     }
 
-    // the sigma_t and source pools carry kPoolPad elements of padding on both sides
-    char* st_ptr() const { return (char*)d_st.p + (size_t)kPoolPad * esz; }
-    char* src_ptr() const { return (char*)d_src.p + (size_t)kPoolPad * esz; }
+    // shape of problem p's row-scan tasks, ordinates per wavefront
+    ScanShape scan_shape(int p) const
+    {
+        return sW == kScanWaves ? ScanShape{sG, sC, 1, 1} : scan_class_shape(scan_class(probs[p].nx));
+    }
+    int scan_ords(int p) const
+    {
+        const ScanShape sh = scan_shape(p);
+        return kWave / sh.G * sh.K;
+    }
+
+    char* st_ptr() const { return (char*)d_st.p + (size_t)pad * esz; }
+    char* src_ptr() const { return (char*)d_src.p + (size_t)pad * esz; }
+
+    ScanArgs scan_args(int mode_all) const
+    {
+        ScanArgs a{};
+        a.tasks = d_stasks.as<ScanTaskDev>();
+        a.ords = d_lanes.as<LaneDev>();
+        a.next = d_uflags.as<int32_t>();
+        a.sigma_t = st_ptr();
+        a.src = src_ptr();
+        a.part = d_part.p;
+        a.inflow = d_inflow.p;
+        a.ctl = d_ctl.as<Ctl>();
+        a.sysctl = d_sysctl.as<SysCtl>();
+        a.mode_all = mode_all;
+        a.mom_r = mom_r;
+        return a;
+    }
 
     DiagArgs diag_args(int mode_all) const
     {
@@ -397,6 +435,7 @@ struct Plan {
     // one sweep of every running system, with the plan's kernel
     hipError_t launch_sweep_any(int mode_all, hipStream_t s) const
     {
+        if (kind == kSweepScan) return launch_scan(scan_args(mode_all), (int)stasks.size(), sW, fp64, sG, sC, inflow_len > 0, s);
         if (kind == ROM_SWEEP_DIAG) return launch_diag(diag_args(mode_all), grid, dNB, fp64, dR, dK, aniso, s);
         return launch_sweep(sweep_args(mode_all, 0), grid, fp64, tx, ty, dd, aniso, aniso ? (fp64 ? 1 : 2) : 0, L, nmom, s);
     }
@@ -448,6 +487,7 @@ struct Plan {
         c.mom_r = mom_r;
         c.mode = mode;
         c.max_iter = max_iter;
+        c.clock = kind == kSweepScan ? 1 : 0;
         c.tol = tol;
         c.part = d_part.p;
         c.phi = d_phi.p;
@@ -634,6 +674,48 @@ std::vector<double> diag_inflow_table(const Plan& P, const std::vector<SysInput>
     return inf;
 }
 
+// Row-scan sweep: unweighted inflow of every wavefront's ordinates on its entry faces in sweep
+// order: x-face [ny + 2 kScanAhead][NO], y-face [NO][strips G C].
+std::vector<double> scan_inflow_table(const Plan& P, const std::vector<SysInput>& in)
+{
+    std::vector<double> inf(P.inflow_len, 0.0);
+    for (const ScanTaskDev& t : P.stasks) {
+        if (t.xin_off < 0) continue;
+        const int p = P.sys[t.sys].prob, NO = P.scan_ords(p), GC = P.scan_shape(p).strips * P.scan_shape(p).G * P.scan_shape(p).C;
+        rom_handle* h = P.handles[p];
+        const int nx = h->grid.nx, ny = h->grid.ny;
+        const bool xpos = (t.quad == 0 || t.quad == 3), ypos = (t.quad < 2);
+        const int fx = xpos ? ROM_FACE_LEFT : ROM_FACE_RIGHT;
+        const int fy = ypos ? ROM_FACE_BOTTOM : ROM_FACE_TOP;
+        const bool angok = in[t.sys].use_angular;
+        for (int k = 0; k < t.nw * NO; ++k) {
+            const int u = P.user_of[t.sys][P.lanes[t.ord_off + k].ord];
+            if (u < 0) continue;
+            const int64_t xo = t.xin_off + (int64_t)(k / NO) * (ny + 2 * kScanAhead) * NO + k % NO;
+            for (int jj = 0; jj < ny; ++jj) {
+                const int j = ypos ? jj : ny - 1 - jj;
+                if (angok && !h->ang[fx].empty()) inf[xo + (int64_t)jj * NO] = h->ang[fx][(size_t)u * ny + j];
+                else if (!h->face[fx].empty()) inf[xo + (int64_t)jj * NO] = h->face[fx][j];
+            }
+            const int64_t yo = t.yin_off + (int64_t)k * GC;
+            for (int ii = 0; ii < nx; ++ii) {
+                const int i = xpos ? ii : nx - 1 - ii;
+                if (angok && !h->ang[fy].empty()) inf[yo + ii] = h->ang[fy][(size_t)u * nx + i];
+                else if (!h->face[fy].empty()) inf[yo + ii] = h->face[fy][i];
+            }
+        }
+    }
+    return inf;
+}
+
+// The boundary inflow table of a plan's sweep kernel.
+std::vector<double> inflow_table(const Plan& P, const std::vector<SysInput>& in);
+std::vector<double> plan_inflow(const Plan& P, const std::vector<SysInput>& in)
+{
+    return P.kind == kSweepScan ? scan_inflow_table(P, in) : P.kind == ROM_SWEEP_DIAG ? diag_inflow_table(P, in)
+                                                                                      : inflow_table(P, in);
+}
+
 // Boundary inflow of every wave-stream lane in sweep order, scaled by the lane's weight.
 std::vector<double> inflow_table(const Plan& P, const std::vector<SysInput>& in)
 {
@@ -743,7 +825,22 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
             if (si.h->scat_norm) P.mom_r = 1;
     P.esz = P.fp64 ? 8 : 4;
     P.max_iter = max_iter;
-    P.kind = o.sweep == ROM_SWEEP_DIAG ? ROM_SWEEP_DIAG : ROM_SWEEP_STRIP;
+    P.kind = o.sweep == ROM_SWEEP_DIAG || o.sweep == kSweepScan ? o.sweep : ROM_SWEEP_STRIP;
+    int maxnx = 1;
+    for (auto& s : in) maxnx = std::max(maxnx, s.h->grid.nx);
+    if (P.kind == kSweepScan) {
+        if (psi_out || P.dd || P.nmom != 1 || aniso || P.arena) throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: isotropic step sweeps"};
+        P.sG = o.diag_rows;
+        P.sC = o.tile_x;
+        P.sW = o.band;
+        const bool one = P.sW == kScanWaves;
+        if (one ? !scan_supported(P.fp64, P.sG, P.sC) || maxnx > P.sG * P.sC : P.fp64 || (P.sW != 8 && P.sW != 16) || maxnx > kScanMaxNx)
+            throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: shape"};
+        for (auto& s : in)  // the kernel's byte offsets within a system are 32-bit
+            if ((s.h->cells * P.nmom + (4 * kScanAhead + 1) * (int64_t)s.h->grid.nx) * P.esz >= (int64_t)1 << 32)
+                throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: grid too large"};
+        P.pad = std::max<int64_t>(kPoolPad, 2 * kScanAhead * (int64_t)maxnx + 64);
+    }
     if (P.kind == ROM_SWEEP_DIAG) {
         if (psi_out || P.dd || P.nmom != 1 || (aniso && (P.fp64 || max_iter == 0)))
             throw Fail{ROM_E_UNSUPPORTED,
@@ -753,7 +850,8 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
         P.dK = o.diag_k > 0 ? o.diag_k : 1;
         if (!diag_supported(P.fp64, P.dR, P.dK)) throw Fail{ROM_E_ARG, "unsupported row-lane sweep shape"};
     }
-    choose_tiles(o, in, P.fp64, P.tx, P.ty);
+    if (P.kind != kSweepScan) choose_tiles(o, in, P.fp64, P.tx, P.ty);
+    else P.tx = P.ty = 8;  // unused
     if (!(P.fp64 ? sweep_tile_supported_fp64(P.tx, P.ty) : sweep_tile_supported(P.tx, P.ty)))
         throw Fail{ROM_E_ARG, P.fp64 ? "FP64 sweeps support tiles 8x4 and 8x8" : "unsupported tile shape"};
     const int TX = P.tx, TY = P.ty;
@@ -812,6 +910,28 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
                     uflags.push_back(mask);
                 }
             }
+        }
+    }
+
+    // rows whose sigma_t differs from the row before them in sweep order, as the next such row after
+    // each row, for both y directions (the row-scan sweep rebuilds its multipliers there)
+    std::vector<int64_t> next_off(nprob, 0);
+    for (int p = 0; p < nprob && P.kind == kSweepScan; ++p) {
+        rom_handle* h = P.handles[p];
+        const int nx = h->grid.nx, ny = h->grid.ny;
+        next_off[p] = (int64_t)uflags.size();
+        uflags.resize(uflags.size() + 2 * (size_t)ny);
+        int32_t* up = uflags.data() + next_off[p];
+        int32_t* down = up + ny;
+        std::vector<char> differs(ny, 0);  // storage row j against row j - 1
+        for (int j = 1; j < ny; ++j)
+            differs[j] = std::memcmp(&h->st[(size_t)j * nx], &h->st[(size_t)(j - 1) * nx], nx * sizeof(double)) != 0;
+        int32_t nu = INT32_MAX, nd = INT32_MAX;
+        for (int jj = ny - 1; jj >= 0; --jj) {
+            up[jj] = nu;
+            down[jj] = nd;
+            if (differs[jj]) nu = jj;                          // rows jj and jj - 1
+            if (jj > 0 && differs[ny - jj]) nd = jj;           // storage rows ny - 1 - jj and ny - jj
         }
     }
 
@@ -969,6 +1089,63 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     }
     std::vector<std::vector<double>> inv_r(P.nsys);
     for (int s = 0; s < P.nsys; ++s) inv_r[s] = linear_inv_r(in[s].h, in[s]);
+    if (P.kind == kSweepScan) {
+        for (int sy = 0; sy < P.nsys; ++sy) {
+            const int p = P.sys[sy].prob, NO = P.scan_ords(p);
+            rom_handle* h = P.handles[p];
+            const bool inflow = has_inflow(h, in);
+            std::vector<int>& uo = P.user_of[sy];
+            uo.clear();
+            for (int q = 0; q < 4; ++q) {
+                const auto& list = ql[sy].idx[q];
+                // the quadrant's groups in workgroups of at most W wavefronts, evenly
+                const int most = P.sW / P.scan_shape(p).strips;
+                const int nwv = ((int)list.size() + NO - 1) / NO, ngrp = (nwv + most - 1) / most;
+                int wv = 0;
+                for (int gi = 0; gi < ngrp; ++gi) {
+                    ScanTaskDev t{};
+                    t.sys = sy;
+                    t.quad = q;
+                    t.cls = scan_class(h->grid.nx);
+                    t.nx = h->grid.nx;
+                    t.ny = h->grid.ny;
+                    t.nw = nwv / ngrp + (gi < nwv % ngrp ? 1 : 0);
+                    t.field_off = field_off[p];
+                    t.src_off = P.sys[sy].src_off;
+                    t.part_off = part_sum;
+                    t.next_off = next_off[p] + (q < 2 ? 0 : t.ny);
+                    t.ord_off = (int64_t)P.lanes.size();
+                    t.xin_off = t.yin_off = -1;
+                    if (inflow) {
+                        t.xin_off = inflow_sum;
+                        inflow_sum += (int64_t)t.nw * (t.ny + 2 * kScanAhead) * NO;
+                        t.yin_off = inflow_sum;
+                        inflow_sum += (int64_t)t.nw * NO * P.scan_shape(p).strips * P.scan_shape(p).G * P.scan_shape(p).C;
+                    }
+                    for (int k = 0; k < t.nw * NO; ++k) {
+                        const size_t l = (size_t)wv * NO + k;
+                        LaneDev ld{};
+                        ld.ord = (int)uo.size();
+                        const int u = l < list.size() ? list[l] : -1;
+                        uo.push_back(u);
+                        fill_lane(ld, h, in[sy], u, inv_r[sy]);
+                        P.lanes.push_back(ld);
+                    }
+                    wv += t.nw;
+                    P.slot_off.push_back(part_sum);
+                    part_sum += h->cells * P.nmom;
+                    sys_slots[sy].push_back(P.nslots);
+                    ++P.nslots;
+                    P.stasks.push_back(t);
+                }
+            }
+            P.npad_al[sy] = P.sys[sy].npad = (int)uo.size();
+        }
+        // the longest tasks first, so no large one is left for the end of a launch
+        std::stable_sort(P.stasks.begin(), P.stasks.end(), [](const ScanTaskDev& x, const ScanTaskDev& y) {
+            return (int64_t)x.ny * (8 + x.nx / 64) > (int64_t)y.ny * (8 + y.nx / 64);
+        });
+    }
     for (int p = 0; p < nprob && P.kind == ROM_SWEEP_STRIP; ++p) {
         rom_handle* h = P.handles[p];
         const int L = Lp[p], G = 64 / L;
@@ -1078,11 +1255,14 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
         const int V = P.fp64 ? 2 : 4;
         bool aligned = true;
         for (auto& si : in) aligned = aligned && si.h->cells % V == 0;
-        if (maxslots > 8 && P.nmom == 1 && aligned && vec_combine_enabled()) {
+        // large tiles also sum more slots where they fill the GPU twice over: a block's fixed cost
+        // (its count-in and its system's maxima, one address each) then matters more than the split
+        const bool large = tot / (4 * 256 * V) >= 2 * device_cus();
+        if (maxslots > 8 && P.nmom == 1 && aligned && !large && vec_combine_enabled()) {
             P.vec = maxslots > 64 ? 3 : 1;  // 8 waves per block above 64 slots
             P.cells_per_block = 64 * V;
         } else if (P.nmom == 1 && aligned && vec_combine_enabled()) {
-            P.vec = 2;  // few slots: one thread sums all slots of 16 bytes of cells, 4 tiles
+            P.vec = 2;  // one thread sums all slots of 16 bytes of cells, 4 tiles
             P.cells_per_block = 4 * 256 * V;
         } else if (maxslots > 8 && P.nmom == 1) {
             P.many_cpt = 1;
@@ -1110,6 +1290,7 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     put(P, P.d_cblocks, P.cblocks);
     put(P, P.d_uflags, uflags);
     put(P, P.d_dtasks, P.dtasks);
+    put(P, P.d_stasks, P.stasks);
 
     auto cast_upload = [&](DevMem& d, const std::vector<double>& v) {
         if (P.fp64) {
@@ -1130,8 +1311,8 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
         std::copy(h->q.begin(), h->q.end(), qv.begin() + field_off[p]);
     }
     {
-        std::vector<double> padded(fsum + 2 * kPoolPad, 1.0);  // padding: a harmless positive sigma_t
-        std::copy(st.begin(), st.end(), padded.begin() + kPoolPad);
+        std::vector<double> padded(fsum + 2 * P.pad, 1.0);  // padding: a harmless positive sigma_t
+        std::copy(st.begin(), st.end(), padded.begin() + P.pad);
         cast_upload(P.d_st, padded);
     }
     if (!caller_io) {
@@ -1142,16 +1323,15 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     // inflow in sweep order, scaled by the lane weight
     P.inflow_len = inflow_sum;
     if (inflow_sum > 0) {
-        const std::vector<double> inf = P.kind == ROM_SWEEP_DIAG ? diag_inflow_table(P, in) : inflow_table(P, in);
-        cast_upload(P.d_inflow, inf);
+        cast_upload(P.d_inflow, plan_inflow(P, in));
     } else {
         take(P, P.d_inflow, 256);
     }
 
     P.src_len = src_sum;
     if (!caller_io) {
-        take(P, P.d_src, (src_sum + 2 * kPoolPad) * P.esz);
-        zero(P, P.d_src.p, (src_sum + 2 * kPoolPad) * P.esz);
+        take(P, P.d_src, (src_sum + 2 * P.pad) * P.esz);
+        zero(P, P.d_src.p, (src_sum + 2 * P.pad) * P.esz);
         take(P, P.d_phi, phi_sum * P.esz);
     }
     take(P, P.d_part, std::max<int64_t>(part_sum, 1) * P.esz);
@@ -1316,6 +1496,44 @@ bool refresh_ordinates(Plan& P, const std::vector<SysInput>& in, hipStream_t s)
             }
         }
         if (P.aniso) build_kernel_matrices(P, in, s);
+        return true;
+    }
+    if (P.kind == kSweepScan) {
+        // same wavefronts in the same order: refill each one's ordinate entries
+        size_t at = 0;
+        for (int k = 0; k < P.nsys; ++k) {
+            const int NO = P.scan_ords(P.sys[k].prob);
+            rom_handle* h = P.handles[P.sys[k].prob];
+            const std::vector<double> inv_r = linear_inv_r(h, in[k]);
+            std::vector<int>& uo = P.user_of[k];
+            const size_t before = uo.size();
+            uo.clear();
+            for (int q = 0; q < 4; ++q) {
+                const auto& list = ql[k][q];
+                const size_t end = (list.size() + NO - 1) / NO * NO;
+                for (size_t l = 0; l < end; ++l) {
+                    if (at >= P.lanes.size()) throw Fail{ROM_E_STATE, "row-scan task layout changed"};
+                    LaneDev& ld = P.lanes[at++];
+                    const int u = l < list.size() ? list[l] : -1;
+                    ld.ord = (int)uo.size();
+                    uo.push_back(u);
+                    fill_lane(ld, h, in[k], u, inv_r);
+                }
+            }
+            if (uo.size() != before) throw Fail{ROM_E_STATE, "ordinate layout changed"};
+            P.sys_n[k] = in[k].n;
+            P.sys_w[k] = in[k].w;
+        }
+        rewrite(P.d_lanes, P.lanes, s);
+        if (P.inflow_len > 0) {
+            P.h_inflow = scan_inflow_table(P, in);
+            if (P.fp64) {
+                rewrite(P.d_inflow, P.h_inflow, s);
+            } else {
+                P.h_inflow32.assign(P.h_inflow.begin(), P.h_inflow.end());
+                rewrite(P.d_inflow, P.h_inflow32, s);
+            }
+        }
         return true;
     }
     // internal order: quadrant-major, L-lane groups, padded (as built)
@@ -1541,7 +1759,14 @@ SolveResult run_si(Plan& P, hipStream_t s, const rom_si_opts& o)
     for (const SysCtl& c : r.sc) most = std::max(most, c.iter);
     P.last_iters = most;
     r.kind = P.kind;
-    if (P.kind == ROM_SWEEP_DIAG) {
+    if (P.kind == kSweepScan) {
+        // reported among the row-lane sweeps, with lanes = 1
+        r.kind = ROM_SWEEP_DIAG;
+        r.tx = P.scan_shape(0).K;
+        r.ty = P.scan_shape(0).G == 16 ? 16 : 64;
+        r.band = P.sW;
+        r.lanes = 1;
+    } else if (P.kind == ROM_SWEEP_DIAG) {
         r.tx = P.dK;
         r.ty = P.dR;
         r.band = P.dNB;
@@ -2023,6 +2248,10 @@ void apply_choice(const TuneChoice& c, rom_si_opts& o)
         o.tile_x = c.tx;
         o.tile_y = c.ty;
         o.band = c.band;
+    } else if (c.sweep == kSweepScan) {
+        o.tile_x = c.tx;
+        o.diag_rows = c.rows;
+        o.band = c.band;
     } else {
         o.diag_rows = c.rows;
         o.diag_k = c.k;
@@ -2030,9 +2259,36 @@ void apply_choice(const TuneChoice& c, rom_si_opts& o)
     }
 }
 
+// Shapes of the row-scan sweep for a batch (none when a grid is too wide): the single-ordinate form
+// with the fewest cells per lane that hold the widest row, on 16-lane groups too when the rows are
+// short, unless its wavefronts would fill the GPU four times over (512^2, 32 samples of 128
+// ordinates: 775 us per step against 319, with 16 times the partial planes); the form for full GPUs
+// with 8 wavefronts per workgroup, and with 16 where there are enough (512 x 301, 64 samples of 36:
+// 295 us against 560 with 8, for the fewer partial planes; the other way round on small sets).
+std::vector<TuneChoice> scan_choices(const std::vector<SysInput>& in, bool fp64)
+{
+    int maxnx = 0;
+    int64_t ords = 0;
+    for (auto& s : in) {
+        maxnx = std::max(maxnx, s.h->grid.nx);
+        ords += s.n;
+    }
+    std::vector<TuneChoice> c;
+    if (maxnx > kScanMaxNx) return c;
+    const int64_t full = 4 * (int64_t)device_cus();  // one wavefront per SIMD
+    int C = (maxnx + 63) / 64;
+    while (!scan_supported(fp64, 64, C)) ++C;
+    if (fp64 || ords <= 4 * full) c.push_back({kSweepScan, C, 0, kScanWaves, 64, 1});
+    if (maxnx <= 64 && (fp64 || ords <= 16 * full)) c.push_back({kSweepScan, 4, 0, kScanWaves, 16, 1});
+    if (!fp64) c.push_back({kSweepScan, 0, 0, 8, 0, 0});
+    if (!fp64 && ords >= 2 * full) c.push_back({kSweepScan, 0, 0, 16, 0, 0});
+    return c;
+}
+
 // Time sweep + combine steps of every candidate on the real buffers of this batch shape (zero
 // sources) and keep the fastest in the owner handle's cache.  Candidates: the strip kernel's tiles x
-// bands, and, for isotropic step-scheme problems, the row-lane kernel's (rows, ordinates per lane).
+// bands, and, for isotropic step-scheme problems, the row-lane kernel's (rows, ordinates per lane) and
+// the row-scan kernel's shapes.
 void autotune(rom_handle* owner, std::vector<SysInput>& in, rom_si_opts& o, int smode, hipStream_t s)
 {
     const bool aniso = smode == 2;
@@ -2047,7 +2303,23 @@ void autotune(rom_handle* owner, std::vector<SysInput>& in, rom_si_opts& o, int 
     }
     const bool fp64 = o.precision == ROM_PREC_FP64;
     std::vector<TuneChoice> cands;
-    if (o.sweep != ROM_SWEEP_DIAG) {
+    // The row-scan kernel: isotropic step sweeps of grids up to kScanMaxNx wide, when the caller
+    // leaves the kernel open.  The strip kernel is not tried beside it: over 110 shapes from 32^2 to
+    // 1024^2, 8 to 4096 ordinates, it was never the fastest (0.27 to 0.85 of the best one's speed).
+    // The row-lane kernel is: it wins where sigma_t changes in every row (the row-scan multipliers
+    // are then rebuilt per row) and for single problems more than 512 cells wide.
+    if (o.sweep == ROM_SWEEP_AUTO && o.scheme == ROM_SCHEME_STEP && smode == 0) {
+        const char* e = std::getenv("ROM_SWEEP_SCAN");  // 0: without it; k: its k-th shape alone (timing and tests)
+        const int which = e ? std::atoi(e) : -1;
+        if (which != 0) cands = scan_choices(in, fp64);
+        if (which > 0 && which <= (int)cands.size()) {
+            owner->tune_cache[key] = {cands[which - 1].sweep, cands[which - 1].tx, 0, cands[which - 1].band, cands[which - 1].rows, 1};
+            apply_choice(cands[which - 1], o);
+            return;
+        }
+    }
+    const bool scan = !cands.empty();
+    if (o.sweep != ROM_SWEEP_DIAG && !scan) {
         const std::vector<std::pair<int, int>> tiles = fp64 ? std::vector<std::pair<int, int>>{{8, 4}, {8, 8}}
                                                             : std::vector<std::pair<int, int>>{{8, 4}, {8, 8}, {16, 8}, {16, 16}};
         for (auto t : tiles)
@@ -2106,7 +2378,7 @@ void autotune(rom_handle* owner, std::vector<SysInput>& in, rom_si_opts& o, int 
                 pick.tx = P.tx;
                 pick.ty = P.ty;
                 pick.band = P.band;
-            } else {
+            } else if (cand.sweep == ROM_SWEEP_DIAG) {
                 pick.band = P.dNB;
             }
         }

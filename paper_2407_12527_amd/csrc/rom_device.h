@@ -94,6 +94,47 @@ struct DiagTaskDev {
     int32_t pad;
 };
 
+// Task of the row-scan sweep: the whole grid of one problem for nw groups of NO = (64 / G) K
+// ordinates of one quadrant of one system, one wavefront per group and strip (one workgroup, one
+// partial-flux slot).  It
+// holds everything the workgroup needs, so its first loads wait on one table read.
+constexpr int kScanAhead = 8;   // most rows the row-scan sweep fetches ahead (and sums per batch)
+constexpr int kScanWaves = 4;   // wavefronts per workgroup of its single-ordinate form
+constexpr int kScanMaxNx = 1024;
+
+// Shape of a row-scan task: G lanes per strip of a row, C cells per lane, K ordinates per lane group,
+// strips per row (one wavefront each).
+struct ScanShape {
+    int G, C, K, strips;
+};
+
+// Shapes of the form for full GPUs by the problem's width: the narrowest row that fits, 16 (C K)
+// values of each multiplier per lane, so every shape needs about the same registers.
+__host__ __device__ inline int scan_class(int nx)
+{
+    return nx <= 64 ? 0 : nx <= 128 ? 1 : nx <= 256 ? 2 : nx <= 384 ? 3 : nx <= 512 ? 4 : nx <= 768 ? 5 : 6;
+}
+__host__ __device__ inline ScanShape scan_class_shape(int cls)
+{
+    constexpr ScanShape shape[7] = {{16, 4, 4, 1}, {16, 8, 2, 1}, {32, 8, 2, 1}, {64, 6, 2, 1},
+                                    {64, 8, 2, 1}, {64, 6, 2, 2}, {64, 8, 2, 2}};
+    return shape[cls];
+}
+
+struct ScanTaskDev {
+    int32_t sys, quad;
+    int32_t nx, ny;
+    int32_t nw;                 // groups that hold ordinates
+    int32_t cls;                // scan_class of its problem (the form for full GPUs)
+    int64_t field_off;          // offset of sigma_t in the field pool
+    int64_t src_off;            // offset of the system's source
+    int64_t part_off;           // offset of the partial-flux slot
+    int64_t next_off;           // first entry of its y direction in the list of sigma_t changes
+    int64_t ord_off;            // first of its [nw][NO] lane-table entries
+    int64_t xin_off;            // inflow on the entry x-face [nw][ny + 2 kScanAhead][NO], rows in sweep order; -1 vacuum
+    int64_t yin_off;            // inflow on the entry y-face [nw][NO][strips G C], columns in sweep order; -1 vacuum
+};
+
 // Per-system convergence state, written only by the combine step.
 struct SysCtl {
     unsigned long long dmax_bits;   // max |phi^k - phi^{k-1}| of the running iteration (FP64 bits)

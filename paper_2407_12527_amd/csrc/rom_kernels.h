@@ -59,6 +59,21 @@ struct DiagArgs {
     int64_t wait_ticks;        // real-time clock ticks before a dependency wait gives up
 };
 
+struct ScanArgs {
+    const ScanTaskDev* tasks;  // one workgroup each
+    const LaneDev* ords;       // [wavefronts of all tasks][NO] (padding has w = 0)
+    const int32_t* next;       // per problem, y direction and sweep-order row: the next row whose
+                               // sigma_t differs from the row before it (INT32_MAX: none)
+    const void* sigma_t;       // field pool (T)
+    const void* src;           // source pool (T)
+    void* part;                // partial scalar-flux pool (T)
+    const void* inflow;        // unweighted boundary inflow pool (T)
+    Ctl* ctl;
+    SysCtl* sysctl;
+    int32_t mode_all;
+    int32_t mom_r;             // linear kernel: 1 = also form the 1/r-weighted density (plane 3)
+};
+
 struct CombineArgs {
     const SystemDev* sys;
     const ProblemDev* probs;
@@ -78,8 +93,10 @@ struct CombineArgs {
     int32_t mom_r;             // linear kernel: phi~ comes from plane 3 (else phi~ = phi)
     int32_t vec;               // 16-byte loads (every system's cell count a multiple of 16 B /
                                // sizeof(T)): 1 many slots, tiles of 64 * 16 B of cells split over
-                               // the block's 4 waves by slot (3: 8 waves, above 64 slots); 2 at
-                               // most 8 slots, 4 tiles of 256 * 16 B
+                               // the block's 4 waves by slot (3: 8 waves, above 64 slots); 2 every
+                               // slot by one thread, 4 tiles of 256 * 16 B
+    int32_t clock;             // 1: the sweep before it took no end stamp (row-scan sweeps)
+    int32_t pad;
     double tol;
     const void* part;
     void* phi;
@@ -182,6 +199,11 @@ bool diag_supported(bool fp64, int R, int K);
 int diag_max_nb(bool fp64, int K, bool ang = false);
 size_t diag_lds_bytes(bool fp64, int R, int K, int nb);
 hipError_t launch_diag(const DiagArgs& a, int grid, int nb, bool fp64, int R, int K, bool ang, hipStream_t s);
+// Row-scan sweep, one workgroup per task; inf: boundary inflow tables may be present.  waves =
+// kScanWaves: the single-ordinate form, lane groups of G lanes with C cells each (rows of up to G C
+// cells); 8 or 16: the form for full GPUs (FP32, every task in its scan_class shape).
+bool scan_supported(bool fp64, int G, int C);
+hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int G, int C, bool inf, hipStream_t s);
 hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStream_t s);
 hipError_t launch_sweep_prologue(Ctl* ctl, hipStream_t s);
 hipError_t launch_mark(Ctl* ctl, hipStream_t s);

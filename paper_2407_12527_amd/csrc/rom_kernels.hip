@@ -59,6 +59,14 @@ __device__ void finalize_iteration(const CombineArgs& A)
     if (threadIdx.x == 0) A.ctl->active = s_active;
 }
 
+// A row-scan sweep takes no stamp at its end (its workgroups claim no tickets): it ends where the
+// combine step starts.  Device scope, since another XCD's block reads it in combine_tail.
+__device__ __forceinline__ void combine_clock(const CombineArgs& A)
+{
+    if (A.clock && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(&A.ctl->t_last, wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Block maxima (wave reduction, then across the 4 waves), the per-system FP64 maxima as atomics,
 // and the last block's finalize of the iteration.
 __device__ __forceinline__ void combine_tail(const CombineArgs& A, bool run, int s, double dmax, double pmax)
@@ -96,9 +104,10 @@ __device__ __forceinline__ void combine_tail(const CombineArgs& A, bool run, int
     if (s_last) {
         if (A.mode == 0) finalize_iteration(A);
         if (tid == 0) {
-            if (A.ctl->t_last > A.ctl->t_first && A.ctl->t_first != ~0ull) {
+            const unsigned long long t_last = __hip_atomic_load(&A.ctl->t_last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (t_last > A.ctl->t_first && A.ctl->t_first != ~0ull) {
                 const unsigned long long t0 = A.ctl->t_mark < A.ctl->t_first ? A.ctl->t_mark : A.ctl->t_first;
-                A.ctl->sweep_ticks += A.ctl->t_last - t0;
+                A.ctl->sweep_ticks += t_last - t0;
                 A.ctl->sweeps += 1;
             }
             A.ctl->t_first = ~0ull;
@@ -118,6 +127,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs A)
     // Every block of a launch reads `active` before the last block of the same launch can change
     // it, so either all blocks of this launch return here or none does.
     if (A.mode == 0 && A.ctl->active == 0) return;
+    combine_clock(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -177,6 +187,7 @@ __global__ __launch_bounds__(256) void combine_many_kernel(CombineArgs A)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (A.mode == 0 && A.ctl->active == 0) return;
+    combine_clock(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -265,6 +276,7 @@ __global__ __launch_bounds__(64 * NW) void combine_vec_kernel(CombineArgs A)
     static_assert(NW == 4 || NW == 8, "4 or 8 waves");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (A.mode == 0 && A.ctl->active == 0) return;
+    combine_clock(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -325,12 +337,16 @@ __global__ __launch_bounds__(64 * NW) void combine_vec_kernel(CombineArgs A)
     combine_tail(A, run, s, dmax, pmax);
 }
 
-// Few-slot combine with vector loads (at most 8 slots, e.g. ensembles with one lane group per
-// quadrant): each thread owns 16 bytes of consecutive cells in each of the block's TPB tiles of
-// 256 * 16 bytes; it issues every load of all its tiles (one 16-byte load per slot, plus phi,
-// sigma_s and q) before any arithmetic or store, so a thread keeps up to TPB * 11 loads in flight,
-// and the block's convergence atomics are amortized over TPB tiles.  Slots are added as
-// ((s0 + s1) + (s2 + s3)) + ((s4 + s5) + (s6 + s7)).
+// Large-tile combine with vector loads (at most 8 slots, e.g. ensembles with one lane group per
+// quadrant; more when the plan has cells enough to fill the GPU with such tiles): each thread owns
+// 16 bytes of consecutive cells in each of the block's TPB tiles of 256 * 16 bytes; it issues every
+// load of all its tiles (one 16-byte load per slot, plus phi, sigma_s and q) before any arithmetic
+// or store, so a thread keeps up to TPB * 11 loads in flight, and the block's convergence atomics
+// are amortized over TPB tiles.  Slots are added as ((s0 + s1) + (s2 + s3)) + ((s4 + s5) + (s6 + s7)),
+// further ones eight at a time the same way onto the running sum.  Bound by memory; what a block
+// costs beyond it is its count-in on one counter, about 10 ns each when they arrive together, so a
+// batch of 24 problems up to 1024^2 with 9 to 64 slots each takes 1024-cell blocks (25 000 of them)
+// 570 us a step, and these 4096-cell ones a quarter of that.
 constexpr int kFewTiles = 4;
 
 template <typename T>
@@ -340,6 +356,7 @@ __global__ __launch_bounds__(256) void combine_vec_few_kernel(CombineArgs A)
     constexpr int V = 16 / sizeof(T);
     constexpr int TPB = kFewTiles;
     if (A.mode == 0 && A.ctl->active == 0) return;
+    combine_clock(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -359,7 +376,7 @@ __global__ __launch_bounds__(256) void combine_vec_few_kernel(CombineArgs A)
         const T* sp[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) sp[k] = k < ns ? part + soff[sord[k]] : nullptr;
-        V4 acc[TPB][8], old[TPB], ssv[TPB], qv[TPB];
+        V4 acc[TPB][8], old[TPB], ssv[TPB], qv[TPB], sum[TPB];
 #pragma unroll
         for (int t = 0; t < TPB; ++t) {
             const int c0 = blk.y + t * 256 * V + (int)threadIdx.x * V;
@@ -371,11 +388,26 @@ __global__ __launch_bounds__(256) void combine_vec_few_kernel(CombineArgs A)
             qv[t] = (in && A.mode == 0) ? *(const V4*)(qp + c0) : V4{};
         }
 #pragma unroll
+        for (int t = 0; t < TPB; ++t)
+            sum[t] = ((acc[t][0] + acc[t][1]) + (acc[t][2] + acc[t][3])) + ((acc[t][4] + acc[t][5]) + (acc[t][6] + acc[t][7]));
+        for (int k0 = 8; k0 < ns; k0 += 8) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sp[k] = k0 + k < ns ? part + soff[sord[k0 + k]] : nullptr;
+#pragma unroll
+            for (int t = 0; t < TPB; ++t) {
+                const int c0 = blk.y + t * 256 * V + (int)threadIdx.x * V;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) acc[t][k] = (c0 < cells && k0 + k < ns) ? *(const V4*)(sp[k] + c0) : V4{};
+            }
+#pragma unroll
+            for (int t = 0; t < TPB; ++t)
+                sum[t] += ((acc[t][0] + acc[t][1]) + (acc[t][2] + acc[t][3])) + ((acc[t][4] + acc[t][5]) + (acc[t][6] + acc[t][7]));
+        }
+#pragma unroll
         for (int t = 0; t < TPB; ++t) {
             const int c0 = blk.y + t * 256 * V + (int)threadIdx.x * V;
             if (c0 >= cells) continue;
-            const V4 tot = ((acc[t][0] + acc[t][1]) + (acc[t][2] + acc[t][3])) +
-                           ((acc[t][4] + acc[t][5]) + (acc[t][6] + acc[t][7]));
+            const V4 tot = sum[t];
             const T* tv = (const T*)&tot;
             const T* ov = (const T*)&old[t];
             const T* sv = (const T*)&ssv[t];
@@ -405,6 +437,7 @@ __global__ __launch_bounds__(256) void combine_moments_kernel(CombineArgs A)
 {
     const int tid = threadIdx.x;
     if (A.mode == 0 && A.ctl->active == 0) return;
+    combine_clock(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -1066,6 +1099,23 @@ hipError_t launch_diag(const DiagArgs& a, int grid, int nb, bool fp64, int R, in
 {
     if (!diag_supported(fp64, R, K) || (ang && fp64)) return hipErrorInvalidValue;
     return fp64 ? launch_diag_f64(a, grid, nb, R, K, s) : launch_diag_f32(a, grid, nb, R, K, ang, s);
+}
+
+hipError_t launch_scan_f32(const ScanArgs&, int, int, int, bool, hipStream_t);
+hipError_t launch_scan_f64(const ScanArgs&, int, int, int, bool, hipStream_t);
+hipError_t launch_scan_f32_many(const ScanArgs&, int, int, bool, hipStream_t);
+
+bool scan_supported(bool fp64, int G, int C)
+{
+    if (G == 16) return C == 4;
+    return G == 64 && ((C >= 1 && C <= 4) || C == 6 || C == 8 || C == 16 || (!fp64 && (C == 5 || C == 12)));
+}
+
+hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int G, int C, bool inf, hipStream_t s)
+{
+    if (waves != kScanWaves) return fp64 ? hipErrorInvalidValue : launch_scan_f32_many(a, ntasks, waves, inf, s);
+    if (!scan_supported(fp64, G, C)) return hipErrorInvalidValue;
+    return fp64 ? launch_scan_f64(a, ntasks, G, C, inf, s) : launch_scan_f32(a, ntasks, G, C, inf, s);
 }
 
 hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStream_t s)

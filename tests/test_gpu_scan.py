@@ -1,0 +1,126 @@
+"""GPU parity of the row-scan sweep kernel (chosen by the autotuner only) against the FP64 oracle.
+
+ROM_SWEEP_SCAN=k makes the autotuner take the k-th row-scan shape of a problem: the single-ordinate
+forms first, then (FP32) the form for full GPUs with 8 and 16 wavefronts per workgroup.  Widths sit at
+the edges of the shapes (lane groups of 16, 32 and 64, 1 to 16 cells per lane, one and two strips per
+row, rows that end inside a 16-byte store), heights at the edges of a batch of rows; sigma_t changes
+in every row, in bands of rows, or not at all.  Bars as in the other parity tests at a fixed iteration
+count: FP32 1e-5 (per cell 1e-4), FP64 1e-11."""
+import numpy as np
+import pytest
+
+import parity
+
+pytestmark = pytest.mark.gpu
+
+FACES = ("left", "right", "bottom", "top")
+
+
+@pytest.fixture(scope="module")
+def R():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_12527_amd import rom
+    rom.lib()
+    return rom
+
+
+def problem(rng, nx, ny, medium):
+    if medium == "random":
+        st = rng.uniform(0.2, 8.0, (ny, nx))
+    elif medium == "bands":
+        st = np.repeat(rng.uniform(0.2, 8.0, -(-ny // 7)), 7)[:ny, None] * (1.0 + np.arange(nx) // 5 % 2)
+    else:
+        st = np.full((ny, nx), 1.3)
+    return st.ravel(), (st * rng.uniform(0.0, 0.9, (ny, nx))).ravel(), rng.uniform(0.0, 1.0, nx * ny)
+
+
+def shapes(fp64, nx, n):
+    """How many row-scan shapes a problem of that width has, and those of the form for full GPUs."""
+    one = 2 if nx <= 64 else 1
+    return one if fp64 else one + 1 + (1 if n >= 2048 else 0)
+
+
+def compare(R, orc, nx, ny, n, prec, medium, inflow, angular=False):
+    rng = np.random.default_rng([nx, ny, n])
+    st, ss, q = problem(rng, nx, ny, medium)
+    infl = {f: rng.uniform(0, 1, ny if f in FACES[:2] else nx) for f in FACES} if inflow else None
+    box = (0.0, 1.5, 0.0, 0.7)
+    h = R.Handle(nx, ny, st, ss, q, box=box, inflow=infl)
+    d, w = R.generate_ordinates(R.ROM_ORD_IID_SPHERE, n, seed=nx + ny)
+    h.set_ordinates(d, w)
+    ang = None
+    if angular:
+        ang = {0: rng.uniform(0, 1, (n, ny)), 3: rng.uniform(0, 1, (n, nx))}
+        for f, v in ang.items():
+            h.set_inflow_angular(f, v)
+    fp64 = prec == "fp64"
+    phi, s, _ = h.source_iterate(R.si_opts(tol=-1, max_iter=4, precision=R.ROM_PREC_FP64 if fp64 else R.ROM_PREC_FP32))
+    assert s.sweep == R.ROM_SWEEP_DIAG and s.lanes == 1  # a row-scan sweep
+    assert s.sweeps == 4 and s.sweep_ms > 0
+    p = orc.Problem(nx, ny, st, ss, q, box=box, inflow=infl, inflow_angular={FACES[f]: v for f, v in ang.items()} if ang else None)
+    ref = orc.source_iterate(p, d, w, None, tol=-1, max_iter=4)["phi"]
+    parity.check(phi, ref, 1e-11 if fp64 else 1e-5)
+
+
+WIDTHS = [1, 3, 16, 63, 64, 65, 127, 128, 130, 192, 256, 257, 300, 320, 384, 385, 511, 512, 513, 700, 768, 769, 1023, 1024]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx", WIDTHS)
+def test_widths(R, orc, monkeypatch, nx, prec):
+    for k in range(shapes(prec == "fp64", nx, 0)):
+        monkeypatch.setenv("ROM_SWEEP_SCAN", str(k + 1))
+        for ny, n, medium, inflow in ((33, 29, "random", False), (16, 41, "bands", True), (1, 3, "uniform", False)):
+            compare(R, orc, nx, ny, n, prec, medium, inflow)
+
+
+@pytest.mark.parametrize("ny", [2, 7, 8, 9, 23])
+@pytest.mark.parametrize("nx,n", [(20, 70), (100, 140), (200, 9), (600, 33)])
+def test_heights_and_angular_inflow(R, orc, monkeypatch, nx, ny, n):
+    for k in range(shapes(False, nx, 0)):
+        monkeypatch.setenv("ROM_SWEEP_SCAN", str(k + 1))
+        compare(R, orc, nx, ny, n, "fp32", "bands", False, angular=True)
+
+
+@pytest.mark.parametrize("nx,ny", [(48, 31), (90, 20), (257, 12)])
+def test_sixteen_wavefronts(R, orc, monkeypatch, nx, ny):
+    n = 2052
+    monkeypatch.setenv("ROM_SWEEP_SCAN", str(shapes(False, nx, n)))
+    compare(R, orc, nx, ny, n, "fp32", "bands", True)
+
+
+@pytest.mark.parametrize("k", [1, 2])
+def test_uneven_batch_and_new_ordinates(R, orc, monkeypatch, k):
+    """A batch of every width class in one launch; then other ordinates (counts kept) on the same plan."""
+    monkeypatch.setenv("ROM_SWEEP_SCAN", str(k))
+    rng = np.random.default_rng(5)
+    hs, ps, opts = [], [], R.si_opts(tol=-1, max_iter=3)
+    for nx, ny in ((40, 19), (100, 33), (256, 9), (350, 21), (512, 8), (700, 17), (1024, 10)):
+        st, ss, q = problem(rng, nx, ny, "bands")
+        hs.append(R.Handle(nx, ny, st, ss, q))
+        ps.append(orc.Problem(nx, ny, st, ss, q))
+    for seed in (1, 2):
+        sets = [R.generate_ordinates(R.ROM_ORD_STRATIFIED, 1 + i % 3, 3, seed=seed, sample=i) for i in range(len(hs))]
+        for h, (d, w) in zip(hs, sets):
+            h.set_ordinates(d, w)
+        outs, stats, _ = R.solve_batch(hs, opts)
+        for p, (d, w), phi, s in zip(ps, sets, outs, stats):
+            assert s.lanes == 1
+            parity.check(phi, orc.source_iterate(p, d, w, None, tol=-1, max_iter=3)["phi"], 1e-5)
+
+
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_ensemble(R, orc, monkeypatch, k):
+    monkeypatch.setenv("ROM_SWEEP_SCAN", str(k))
+    rng = np.random.default_rng(9)
+    st, ss, q = problem(rng, 50, 37, "bands")
+    h = R.Handle(50, 37, st, ss, q)
+    p = orc.Problem(50, 37, st, ss, q)
+    for seed in (3, 4):  # the second call refreshes the plan's tables
+        phis, s, _ = h.ensemble_samples(5, seed, R.ROM_ORD_STRATIFIED, 2, 3, opts=R.si_opts(tol=-1, max_iter=4))
+        assert s.lanes == 1
+        for i in range(5):
+            d, w = R.generate_ordinates(R.ROM_ORD_STRATIFIED, 2, 3, seed=seed, sample=i)
+            parity.check(phis[i], orc.source_iterate(p, d, w, None, tol=-1, max_iter=4)["phi"], 1e-5)
