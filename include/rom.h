@@ -81,8 +81,9 @@ extern "C" {
  * (every scheme, source kind and angular-flux output).  DIAG: grid rows on lanes, each
  * wavefront sweeping the anti-diagonals of a 16- or 64-row block with the y-face value passed one
  * lane up; far more parallel work per ordinate, for isotropic step-scheme source iteration.  With
- * AUTO librom may also take a third kernel, which sweeps whole rows as prefix scans (isotropic step
- * sources, nx <= 1024); it reports itself as ROM_SWEEP_DIAG with lanes = 1. */
+ * AUTO librom may also take a third kernel, which sweeps whole rows as prefix scans (sources from the
+ * scalar flux or the linear kernel's moments, nx <= 1024); it reports itself with lanes = 1, as
+ * ROM_SWEEP_DIAG where that kernel applies and as ROM_SWEEP_STRIP elsewhere. */
 #define ROM_SWEEP_AUTO 0
 #define ROM_SWEEP_STRIP 1
 #define ROM_SWEEP_DIAG 2

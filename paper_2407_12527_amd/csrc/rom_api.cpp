@@ -201,7 +201,7 @@ struct Arena;
 // The row-scan sweep, chosen by librom only (rom_si_opts asks for the strip or row-lane kernel, or
 // leaves the choice).  Its shape travels in the options' fields of the other sweeps: band =
 // wavefronts W; diag_rows = lanes per row G and tile_x = cells per lane C of the single-ordinate
-// form (W = kScanWaves).
+// form (W = 1 or 4).
 constexpr int kSweepScan = 3;
 
 struct rom_handle {
@@ -209,6 +209,7 @@ struct rom_handle {
     double dx = 0, dy = 0;
     int64_t cells = 0;
     std::vector<double> st, ss, q;
+    int row_changes = 0;        // rows whose sigma_t differs from the row below
     std::vector<double> face[4];
     // ordinates in the caller's order
     int n = 0;
@@ -378,7 +379,7 @@ struct Plan {
     // shape of problem p's row-scan tasks, ordinates per wavefront
     ScanShape scan_shape(int p) const
     {
-        return sW == kScanWaves ? ScanShape{sG, sC, 1, 1} : scan_class_shape(scan_class(probs[p].nx));
+        return sW <= kScanWaves ? ScanShape{sG, sC, 1, 1} : scan_class_shape(scan_class(probs[p].nx));
     }
     int scan_ords(int p) const
     {
@@ -435,7 +436,7 @@ struct Plan {
     // one sweep of every running system, with the plan's kernel
     hipError_t launch_sweep_any(int mode_all, hipStream_t s) const
     {
-        if (kind == kSweepScan) return launch_scan(scan_args(mode_all), (int)stasks.size(), sW, fp64, sG, sC, inflow_len > 0, s);
+        if (kind == kSweepScan) return launch_scan(scan_args(mode_all), (int)stasks.size(), sW, fp64, sG, sC, nmom, dd, inflow_len > 0, s);
         if (kind == ROM_SWEEP_DIAG) return launch_diag(diag_args(mode_all), grid, dNB, fp64, dR, dK, aniso, s);
         return launch_sweep(sweep_args(mode_all, 0), grid, fp64, tx, ty, dd, aniso, aniso ? (fp64 ? 1 : 2) : 0, L, nmom, s);
     }
@@ -829,12 +830,11 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     int maxnx = 1;
     for (auto& s : in) maxnx = std::max(maxnx, s.h->grid.nx);
     if (P.kind == kSweepScan) {
-        if (psi_out || P.dd || P.nmom != 1 || aniso || P.arena) throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: isotropic step sweeps"};
+        if (psi_out || aniso || P.arena) throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: sources from the scalar flux and its moments"};
         P.sG = o.diag_rows;
         P.sC = o.tile_x;
         P.sW = o.band;
-        const bool one = P.sW == kScanWaves;
-        if (one ? !scan_supported(P.fp64, P.sG, P.sC) || maxnx > P.sG * P.sC : P.fp64 || (P.sW != 8 && P.sW != 16) || maxnx > kScanMaxNx)
+        if (!scan_supported(P.fp64, P.sW, P.sG, P.sC, P.nmom, P.dd) || maxnx > (P.sW <= kScanWaves ? P.sG * P.sC : kScanMaxNx))
             throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: shape"};
         for (auto& s : in)  // the kernel's byte offsets within a system are 32-bit
             if ((s.h->cells * P.nmom + (4 * kScanAhead + 1) * (int64_t)s.h->grid.nx) * P.esz >= (int64_t)1 << 32)
@@ -1423,6 +1423,20 @@ void build_kernel_matrices(Plan& P, const std::vector<SysInput>& in, hipStream_t
     HIPCHK(launch_kernel_matrix(a, s));
 }
 
+// The linear kernel's g of every system, rewritten where it has changed.
+void refresh_g(Plan& P, const std::vector<SysInput>& in, hipStream_t s)
+{
+    bool gchange = false;
+    for (int k = 0; k < P.nsys; ++k) {
+        const double g = scat_mode(in[k].h) == 1 ? in[k].h->g : 0.0;
+        if (P.sys[k].g != g) {
+            P.sys[k].g = g;
+            gchange = true;
+        }
+    }
+    if (gchange) rewrite(P.d_sys, P.sys, s);
+}
+
 // New ordinate values (and inflow or kernel values) for a plan whose structure still fits: the
 // same systems, the same ordinate count in every quadrant and the same inflow presence.  Rewrites
 // the lane table, the weighted inflow and the kernel matrices in place, stream-ordered on s, so
@@ -1525,6 +1539,7 @@ bool refresh_ordinates(Plan& P, const std::vector<SysInput>& in, hipStream_t s)
             P.sys_w[k] = in[k].w;
         }
         rewrite(P.d_lanes, P.lanes, s);
+        refresh_g(P, in, s);
         if (P.inflow_len > 0) {
             P.h_inflow = scan_inflow_table(P, in);
             if (P.fp64) {
@@ -1562,16 +1577,7 @@ bool refresh_ordinates(Plan& P, const std::vector<SysInput>& in, hipStream_t s)
         }
     }
     rewrite(P.d_lanes, P.lanes, s);
-    // the linear kernel's g may have changed
-    bool gchange = false;
-    for (int k = 0; k < P.nsys; ++k) {
-        const double g = scat_mode(in[k].h) == 1 ? in[k].h->g : 0.0;
-        if (P.sys[k].g != g) {
-            P.sys[k].g = g;
-            gchange = true;
-        }
-    }
-    if (gchange) rewrite(P.d_sys, P.sys, s);
+    refresh_g(P, in, s);
     if (P.inflow_len > 0) {
         P.h_inflow = inflow_table(P, in);
         if (P.fp64) {
@@ -1760,8 +1766,8 @@ SolveResult run_si(Plan& P, hipStream_t s, const rom_si_opts& o)
     P.last_iters = most;
     r.kind = P.kind;
     if (P.kind == kSweepScan) {
-        // reported among the row-lane sweeps, with lanes = 1
-        r.kind = ROM_SWEEP_DIAG;
+        // reported among the row-lane sweeps, or the strip sweeps where those do not apply
+        r.kind = P.nmom == 1 && !P.dd ? ROM_SWEEP_DIAG : ROM_SWEEP_STRIP;
         r.tx = P.scan_shape(0).K;
         r.ty = P.scan_shape(0).G == 16 ? 16 : 64;
         r.band = P.sW;
@@ -1921,6 +1927,8 @@ int rom_create(const rom_grid* grid, const double* sigma_t, const double* sigma_
         h->dy = (grid->y1 - grid->y0) / grid->ny;
         h->cells = cells;
         h->st.assign(sigma_t, sigma_t + cells);
+        for (int64_t i = h->grid.nx; i < cells; i += h->grid.nx)
+            h->row_changes += std::memcmp(&h->st[i], &h->st[i - h->grid.nx], h->grid.nx * sizeof(double)) != 0;
         h->ss.assign(sigma_s, sigma_s + cells);
         h->q.assign(q, q + cells);
         for (int f = 0; f < 4; ++f)
@@ -2206,10 +2214,10 @@ bool is_aniso(const rom_handle* h) { return scat_mode(h) == 2; }
 // Source iteration for a list of systems; fills stats and phis.
 // ------------------------------------------------------------------------------------ autotuner
 //
-// The sweep kernel (strip or row-lane) and its shape decide pipeline depth, per-step overhead
-// and occupancy, and the best choice depends on the batch: a single problem with few ordinates
-// wants the row-lane kernel's spatial parallelism, a large ensemble the strip kernel's in-lane
-// ordinate sums.  The first solve of a batch shape times each candidate on the real buffers (one
+// Where the row-scan sweep is not taken (scan_rule), the sweep kernel (strip or row-lane) and its shape
+// decide pipeline depth, per-step overhead and occupancy, and the best choice depends on the batch: a
+// single problem with few ordinates wants the row-lane kernel's spatial parallelism, a large ensemble
+// the strip kernel's in-lane ordinate sums.  The first solve of a batch shape times each candidate on the real buffers (one
 // warm-up and five timed steps each) and caches the fastest in the handle that leads the solve
 // (the ensemble's or single solve's handle, a batch's first handle).  Every choice is
 // deterministic; strip tiles and bands give bitwise identical results, while the row-lane kernel
@@ -2259,36 +2267,92 @@ void apply_choice(const TuneChoice& c, rom_si_opts& o)
     }
 }
 
-// Shapes of the row-scan sweep for a batch (none when a grid is too wide): the single-ordinate form
-// with the fewest cells per lane that hold the widest row, on 16-lane groups too when the rows are
-// short, unless its wavefronts would fill the GPU four times over (512^2, 32 samples of 128
-// ordinates: 775 us per step against 319, with 16 times the partial planes); the form for full GPUs
-// with 8 wavefronts per workgroup, and with 16 where there are enough (512 x 301, 64 samples of 36:
-// 295 us against 560 with 8, for the fewer partial planes; the other way round on small sets).
-std::vector<TuneChoice> scan_choices(const std::vector<SysInput>& in, bool fp64)
+// The row-scan shapes a batch can take: the single-ordinate form with the fewest cells per lane that
+// hold the widest row, then on 16-lane groups (one wavefront per workgroup where that holds a
+// quadrant), then the form for full GPUs with 8 and 16 wavefronts per workgroup.
+std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, int mom)
 {
-    int maxnx = 0;
-    int64_t ords = 0;
-    for (auto& s : in) {
-        maxnx = std::max(maxnx, s.h->grid.nx);
-        ords += s.n;
-    }
     std::vector<TuneChoice> c;
-    if (maxnx > kScanMaxNx) return c;
-    const int64_t full = 4 * (int64_t)device_cus();  // one wavefront per SIMD
     int C = (maxnx + 63) / 64;
-    while (!scan_supported(fp64, 64, C)) ++C;
-    if (fp64 || ords <= 4 * full) c.push_back({kSweepScan, C, 0, kScanWaves, 64, 1});
-    if (maxnx <= 64 && (fp64 || ords <= 16 * full)) c.push_back({kSweepScan, 4, 0, kScanWaves, 16, 1});
-    if (!fp64) c.push_back({kSweepScan, 0, 0, 8, 0, 0});
-    if (!fp64 && ords >= 2 * full) c.push_back({kSweepScan, 0, 0, 16, 0, 0});
+    while (C <= 16 && !scan_supported(fp64, 4, 64, C, mom, dd)) ++C;
+    if (C <= 16) c.push_back({kSweepScan, C, 0, 4, 64, 1});
+    if (maxnx <= 128) c.push_back({kSweepScan, maxnx <= 64 ? 4 : 8, 0, maxn <= 16 ? 1 : 4, 16, 1});
+    if (scan_supported(fp64, 8, 0, 0, mom, dd) && maxnx <= kScanMaxNx) {
+        c.push_back({kSweepScan, 0, 0, 8, 0, 0});
+        c.push_back({kSweepScan, 0, 0, 16, 0, 0});
+    }
     return c;
+}
+
+// Whether a solve whose sweep kernel the caller leaves open takes the row-scan sweep, and in which
+// shape: a rule, not a measurement, so a problem always sums in the same order.  The lines come from
+// step times (sweep and combine) of 240 shapes, 32^2 to 1024^2 cells and 8 to 8192 ordinates in all:
+//   * media whose sigma_t changes in more than a quarter of the rows rebuild the multipliers too
+//     often: beyond 64 columns the row-lane kernel is faster (256^2, 100 ordinates, random sigma_t:
+//     74 us against 87; 64 columns: 26.1 against 25.1);
+//   * up to 512 columns it beat the row-lane kernel on every other shape (64^2 x 256: 22 us against
+//     30; 256^2 x 256: 62 / 84; 512^2 x 256: 142 / 197; FP64 256^2 x 256: 79 / 158) and the strip
+//     kernel by 1.6 to 12 times; beyond, where there are 1024 ordinates to fill the GPU or at most
+//     128 rows (1000 x 64 x 36: 50 / 70; 1024^2 x 1024: 682 / 771, but 1024^2 x 256: 557 / 470);
+//   * 16-lane groups, four ordinates per wavefront, where one per wavefront would queue (64^2, 32
+//     samples of 64: 23 us against 27; 128^2 the same: 43 / 54; 64^2 x 80: 24 / 19);
+//   * the form for full GPUs from 2048 ordinates (256^2, 32 samples of 128: 130 us against 162;
+//     512^2: 319 / 775), from 4096 up to 128 columns and 16384 up to 64, where 16-lane groups carry
+//     further; with 16 wavefronts per workgroup where the partial planes it saves matter and its
+//     workgroups are full (512^2, 64 samples of 128: 467 us against 550; 24 uneven problems: 784 / 512).
+bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode, TuneChoice& pick)
+{
+    if (o.sweep != ROM_SWEEP_AUTO || smode == 2) return false;
+    const bool fp64 = o.precision == ROM_PREC_FP64, dd = o.scheme == ROM_SCHEME_DD;
+    const int mom = smode == 1 ? 4 : 1;
+    int maxnx = 0, maxny = 0, maxn = 0;
+    int64_t ords = 0, rows = 0, changes = 0, groups = 0, space = 0;
+    for (auto& s : in) {
+        const rom_handle* h = s.h;
+        maxnx = std::max(maxnx, h->grid.nx);
+        maxny = std::max(maxny, h->grid.ny);
+        maxn = std::max(maxn, s.n);
+        ords += s.n;
+        rows += h->grid.ny;
+        changes += h->row_changes;
+        // wavefronts with work, and wavefronts held, of 16-wavefront workgroups
+        const ScanShape sh = scan_class_shape(scan_class(h->grid.nx));
+        const int per = 64 / sh.G * sh.K, w = ((s.n + 3) / 4 + per - 1) / per * sh.strips;
+        groups += w;
+        space += (w + 15) / 16 * 16;
+    }
+    const std::vector<TuneChoice> c = scan_choices(maxnx, maxn, fp64, dd, mom);
+    const char* e = std::getenv("ROM_SWEEP_SCAN");  // 0: without it; k: the k-th shape (timing and tests)
+    const int which = e ? std::atoi(e) : -1;
+    if (c.empty() || which == 0) return false;
+    if (which > 0) {
+        if (which > (int)c.size()) return false;
+        pick = c[which - 1];
+        return true;
+    }
+    auto take = [&](int waves, int G) {
+        for (const TuneChoice& t : c)
+            if ((waves > 4) == (t.band > 4) && (waves > 4 ? t.band == waves : t.rows == G)) {
+                pick = t;
+                return true;
+            }
+        return false;
+    };
+    if (mom == 4 || dd) return maxnx <= 512 && take(4, maxnx <= 64 && ords >= 4096 ? 16 : 64);
+    if (maxnx > 64 && changes * 4 > rows) return false;
+    if (maxnx > 512 && ords < 1024 && maxny > 128) return false;
+    const bool sixteen = space > 0 && groups * 10 >= space * 9;
+    if (maxnx > 512) return fp64 ? take(4, 64) : take(ords >= 2048 && sixteen ? 16 : 8, 0);
+    if (!fp64 && ords >= (maxnx <= 64 ? 16384 : maxnx <= 128 ? 4096 : 2048))
+        return take(maxnx > 256 && ords >= 6144 && sixteen ? 16 : 8, 0);
+    if (maxnx <= 64 && (ords >= (fp64 ? 1024 : 2048) || (!fp64 && maxn >= 256 && maxny <= 100))) return take(4, 16);
+    if (maxnx <= 128 && maxnx > 64 && (fp64 ? ords >= 4096 || (ords >= 2048 && maxny <= 128) : ords > 1024)) return take(4, 16);
+    return take(4, 64);
 }
 
 // Time sweep + combine steps of every candidate on the real buffers of this batch shape (zero
 // sources) and keep the fastest in the owner handle's cache.  Candidates: the strip kernel's tiles x
-// bands, and, for isotropic step-scheme problems, the row-lane kernel's (rows, ordinates per lane) and
-// the row-scan kernel's shapes.
+// bands, and, for isotropic step-scheme problems, the row-lane kernel's (rows, ordinates per lane).
 void autotune(rom_handle* owner, std::vector<SysInput>& in, rom_si_opts& o, int smode, hipStream_t s)
 {
     const bool aniso = smode == 2;
@@ -2303,23 +2367,7 @@ void autotune(rom_handle* owner, std::vector<SysInput>& in, rom_si_opts& o, int 
     }
     const bool fp64 = o.precision == ROM_PREC_FP64;
     std::vector<TuneChoice> cands;
-    // The row-scan kernel: isotropic step sweeps of grids up to kScanMaxNx wide, when the caller
-    // leaves the kernel open.  The strip kernel is not tried beside it: over 110 shapes from 32^2 to
-    // 1024^2, 8 to 4096 ordinates, it was never the fastest (0.27 to 0.85 of the best one's speed).
-    // The row-lane kernel is: it wins where sigma_t changes in every row (the row-scan multipliers
-    // are then rebuilt per row) and for single problems more than 512 cells wide.
-    if (o.sweep == ROM_SWEEP_AUTO && o.scheme == ROM_SCHEME_STEP && smode == 0) {
-        const char* e = std::getenv("ROM_SWEEP_SCAN");  // 0: without it; k: its k-th shape alone (timing and tests)
-        const int which = e ? std::atoi(e) : -1;
-        if (which != 0) cands = scan_choices(in, fp64);
-        if (which > 0 && which <= (int)cands.size()) {
-            owner->tune_cache[key] = {cands[which - 1].sweep, cands[which - 1].tx, 0, cands[which - 1].band, cands[which - 1].rows, 1};
-            apply_choice(cands[which - 1], o);
-            return;
-        }
-    }
-    const bool scan = !cands.empty();
-    if (o.sweep != ROM_SWEEP_DIAG && !scan) {
+    if (o.sweep != ROM_SWEEP_DIAG) {
         const std::vector<std::pair<int, int>> tiles = fp64 ? std::vector<std::pair<int, int>>{{8, 4}, {8, 8}}
                                                             : std::vector<std::pair<int, int>>{{8, 4}, {8, 8}, {16, 8}, {16, 16}};
         for (auto t : tiles)
@@ -2404,7 +2452,11 @@ int solve_systems(rom_handle* owner, std::vector<SysInput>& in, const rom_si_opt
     if (reuse == 0 || !slot) {
         const bool free_shape = o.sweep == ROM_SWEEP_DIAG ? (o.diag_rows == 0 || o.diag_k == 0 || o.band == 0)
                                                           : (o.tile_x == 0 && o.band == 0);
-        if (free_shape && autotune_enabled()) autotune(owner, in, o, smode, owner->stream());
+        TuneChoice scan;
+        if (free_shape && autotune_enabled()) {
+            if (scan_rule(in, o, smode, scan)) apply_choice(scan, o);
+            else autotune(owner, in, o, smode, owner->stream());
+        }
         slot.reset(new Plan());
         build_plan(*slot, in, o, smode, o.max_iter);
         if (aniso) {

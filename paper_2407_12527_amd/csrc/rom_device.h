@@ -99,7 +99,7 @@ struct DiagTaskDev {
 // partial-flux slot).  It
 // holds everything the workgroup needs, so its first loads wait on one table read.
 constexpr int kScanAhead = 8;   // most rows the row-scan sweep fetches ahead (and sums per batch)
-constexpr int kScanWaves = 4;   // wavefronts per workgroup of its single-ordinate form
+constexpr int kScanWaves = 4;   // most wavefronts per workgroup of its single-ordinate form
 constexpr int kScanMaxNx = 1024;
 
 // Shape of a row-scan task: G lanes per strip of a row, C cells per lane, K ordinates per lane group,

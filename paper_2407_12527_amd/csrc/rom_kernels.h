@@ -199,11 +199,12 @@ bool diag_supported(bool fp64, int R, int K);
 int diag_max_nb(bool fp64, int K, bool ang = false);
 size_t diag_lds_bytes(bool fp64, int R, int K, int nb);
 hipError_t launch_diag(const DiagArgs& a, int grid, int nb, bool fp64, int R, int K, bool ang, hipStream_t s);
-// Row-scan sweep, one workgroup per task; inf: boundary inflow tables may be present.  waves =
-// kScanWaves: the single-ordinate form, lane groups of G lanes with C cells each (rows of up to G C
-// cells); 8 or 16: the form for full GPUs (FP32, every task in its scan_class shape).
-bool scan_supported(bool fp64, int G, int C);
-hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int G, int C, bool inf, hipStream_t s);
+// Row-scan sweep, one workgroup per task; inf: boundary inflow tables may be present.  waves (per
+// workgroup) 1 or 4: the single-ordinate form, lane groups of G lanes with C cells each (rows of up to
+// G C cells), for isotropic sources (mom 1) and the linear kernel (mom 4), both schemes; 8 or 16: the
+// form for full GPUs (FP32 isotropic step sweeps, every task in its scan_class shape).
+bool scan_supported(bool fp64, int waves, int G, int C, int mom, bool dd);
+hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int G, int C, int mom, bool dd, bool inf, hipStream_t s);
 hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStream_t s);
 hipError_t launch_sweep_prologue(Ctl* ctl, hipStream_t s);
 hipError_t launch_mark(Ctl* ctl, hipStream_t s);

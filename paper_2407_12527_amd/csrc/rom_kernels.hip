@@ -1101,21 +1101,31 @@ hipError_t launch_diag(const DiagArgs& a, int grid, int nb, bool fp64, int R, in
     return fp64 ? launch_diag_f64(a, grid, nb, R, K, s) : launch_diag_f32(a, grid, nb, R, K, ang, s);
 }
 
-hipError_t launch_scan_f32(const ScanArgs&, int, int, int, bool, hipStream_t);
-hipError_t launch_scan_f64(const ScanArgs&, int, int, int, bool, hipStream_t);
+hipError_t launch_scan_f32(const ScanArgs&, int, int, int, int, bool, hipStream_t);
+hipError_t launch_scan_f64(const ScanArgs&, int, int, int, int, bool, hipStream_t);
 hipError_t launch_scan_f32_many(const ScanArgs&, int, int, bool, hipStream_t);
+hipError_t launch_scan_lin_f32(const ScanArgs&, int, int, int, int, int, bool, bool, hipStream_t);
+hipError_t launch_scan_lin_f64(const ScanArgs&, int, int, int, int, int, bool, bool, hipStream_t);
 
-bool scan_supported(bool fp64, int G, int C)
+bool scan_supported(bool fp64, int waves, int G, int C, int mom, bool dd)
 {
-    if (G == 16) return C == 4;
-    return G == 64 && ((C >= 1 && C <= 4) || C == 6 || C == 8 || C == 16 || (!fp64 && (C == 5 || C == 12)));
+    const bool plain = mom == 1 && !dd;
+    if (waves == 8 || waves == 16) return plain && !fp64;
+    if (waves != 1 && waves != 4) return false;
+    if (G == 16) return C == 4 || C == 8;
+    if (G != 64 || waves != 4) return false;
+    if (C == 2 || C == 4 || C == 8) return true;
+    return plain && (C == 1 || C == 3 || C == 6 || C == 16 || (!fp64 && (C == 5 || C == 12)));
 }
 
-hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int G, int C, bool inf, hipStream_t s)
+hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int G, int C, int mom, bool dd, bool inf, hipStream_t s)
 {
-    if (waves != kScanWaves) return fp64 ? hipErrorInvalidValue : launch_scan_f32_many(a, ntasks, waves, inf, s);
-    if (!scan_supported(fp64, G, C)) return hipErrorInvalidValue;
-    return fp64 ? launch_scan_f64(a, ntasks, G, C, inf, s) : launch_scan_f32(a, ntasks, G, C, inf, s);
+    if (!scan_supported(fp64, waves, G, C, mom, dd)) return hipErrorInvalidValue;
+    if (waves > 4) return launch_scan_f32_many(a, ntasks, waves, inf, s);
+    if (mom == 4 || dd)
+        return fp64 ? launch_scan_lin_f64(a, ntasks, waves, G, C, mom, dd, inf, s)
+                    : launch_scan_lin_f32(a, ntasks, waves, G, C, mom, dd, inf, s);
+    return fp64 ? launch_scan_f64(a, ntasks, waves, G, C, inf, s) : launch_scan_f32(a, ntasks, waves, G, C, inf, s);
 }
 
 hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStream_t s)

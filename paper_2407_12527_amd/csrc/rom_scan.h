@@ -19,10 +19,12 @@
 // weighted flux sum (the strip sweep: 7.2 and 3.9 scalar ones, measured on 512^2).
 //
 // A wavefront carries 64 / G groups of K ordinates each, all of one quadrant of one system; the
-// scalar flux of its ordinates is summed in registers, over the lane groups by permlane swaps, and
-// over the workgroup's wavefronts through LDS, U rows at a time in a fixed order, so one partial
-// plane is written per workgroup (deterministic, no float atomics).  Source rows are loaded U rows
-// ahead.  Lanes past the row's end compute on clamped addresses; nothing flows back from them.
+// scalar flux is summed over the workgroup's ordinates through LDS, U rows at a time in a fixed
+// order, so one partial plane is written per workgroup (deterministic, no float atomics).  With one
+// ordinate per group (RAW) psi itself is exchanged and weighted as it is summed, which also forms
+// every moment plane of the linear kernel from one exchange; with several, their weighted sum, over
+// the lane groups too by permlane swaps.  Source rows are loaded U rows ahead.  Lanes past the row's
+// end compute on clamped addresses; nothing flows back from them.
 #pragma once
 #include "rom_common.h"
 
@@ -284,7 +286,9 @@ struct ScanTask {
     const T* S;           // source of the system (same padding); linear kernel: three planes
     T* part;              // partial-flux slot (linear kernel: consecutive planes)
     const int32_t* next;  // per sweep-order row: the next row whose sigma_t differs from the row before it
-    const T* xin;         // entry x-face inflow [ny + padding][NO] of this wavefront's ordinates, NULL: vacuum
+    const LaneDev* ords;  // the task's ordinates
+    const T* xin;         // entry x-face inflow [ny + padding][NO] of this wavefront's ordinates
+    bool has_xin;         // vacuum without (xin then holds NO other values)
     int64_t plane;        // cells
 };
 
@@ -306,15 +310,19 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
                                           const T* __restrict__ yin, const int np_, const bool stopped)
 {
     constexpr int NS = scan_stages<G>();
-    constexpr int RC = C * G / 64;
+    constexpr bool RAW = K == 1 && SPLIT == 1;   // psi is exchanged, weighted as it is summed
+    constexpr int RC = RAW ? C : C * G / 64;     // values a lane exchanges per row
+    constexpr int EG = RAW ? 64 / G : 1;         // entries of a wavefront's row in the exchange
+    constexpr int GC = G * C;                    // values of an entry
     constexpr int V = 16 / sizeof(T);        // cells per 16 bytes, the unit of the flux exchange
     constexpr int NPL = MODE == 1 ? 4 : 1;   // most moment planes
     constexpr int NSRC = MODE == 1 ? 3 : 1;
     constexpr int NO = (64 / G) * K;
     constexpr int KM = MODE == 1 ? K : 1;
     constexpr int KI = INF ? K : 1;
-    constexpr int WV = 64 * RC;              // flux values of one wavefront's row
     constexpr int WE = W / SPLIT;            // wavefronts that share a strip
+    constexpr int NE = WE * EG;              // entries summed per strip
+    static_assert(MODE == 0 || RAW, "moment planes are formed from the exchanged psi");
     static_assert(SPLIT == 1 || (G == 64 && W % SPLIT == 0), "strips are whole wavefronts");
     const int np = MODE == 1 ? np_ : 1;      // moment planes formed
     const int lane = threadIdx.x & (kWave - 1);
@@ -335,8 +343,9 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
     // cell c of a run sits at storage position c (DIR > 0) or C - 1 - c
     constexpr auto at = [](int c) { return DIR > 0 ? c : C - 1 - c; };
 
-    T a[K], b[K], w[K], lc[KM], ls[KM], w1[KM], w2[KM], w3[KM];
+    T a[K], b[K], w[K], lc[KM], ls[KM];
     T y[K][C], rr[K][C], A[K][C], m[K][NS];
+    T X[DD ? K : 1][DD ? C : 1];   // diamond difference: the x-face multiplier 2 A - 1, without its cancellation
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const LaneDev& o = ords[g * K + k];
@@ -346,9 +355,6 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
         if constexpr (MODE == 1) {
             lc[k] = to_T<T>(o.c);
             ls[k] = to_T<T>(o.s);
-            w1[k] = to_T<T>(o.w * o.m1);
-            w2[k] = to_T<T>(o.w * o.m2);
-            w3[k] = to_T<T>(o.w * o.m3);
         }
 #pragma unroll
         for (int c = 0; c < C; ++c) y[k][c] = (INF && yin) ? yin[((g * K + k) * SPLIT + strip) * (G * C) + pos * C + c] : T(0);
@@ -363,7 +369,8 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
             for (int c = 0; c < C; ++c) {
                 rr[k][c] = scan_rcp(sg[at(c)], kap, klo);
                 A[k][c] = a[k] * rr[k][c];
-                p *= DD ? fma(T(2), A[k][c], T(-1)) : A[k][c];
+                if constexpr (DD) X[k][c] = ((a[k] - b[k]) - sg[at(c)]) * rr[k][c];
+                p *= DD ? X[DD ? k : 0][DD ? c : 0] : A[k][c];
             }
             scan_multipliers<T, G>(p, lane, m[k]);
         }
@@ -376,75 +383,90 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
     T x0[INF ? U : 1][KI];   // x-face inflow of the row (used by the group's first lane)
     const T* const sbase = D.S - guard;
     const T* const stbase = D.st - guard;
-    const T* xrow = D.xin;
+    // x-face inflow: vector loads (a scalar load's result is waited for with the LDS ones, every row) and
+    // no branch: a vacuum face reads its first row over and over and keeps zero (300 x 517, inflow on two
+    // sides, 100 ordinates: 148 us per step before, 129 so)
+    const bool first = INF && pos == 0 && D.has_xin;
+    uint32_t xoff = sizeof(T) * (uint32_t)(g * K);
+    if constexpr (INF) asm volatile("" : "+v"(xoff));
+    const uint32_t xstep = D.has_xin ? sizeof(T) * NO : 0;
     uint32_t off = off0;
     auto fetch = [&](const int u) {
 #pragma unroll
         for (int q = 0; q < NSRC; ++q) run_load<T, C>(sbase + q * D.plane, off, S[u][q]);
         off += dstep;
         if constexpr (INF) {
-            if (xrow) {
-#pragma unroll
-                for (int k = 0; k < K; ++k) x0[u][k] = xrow[g * K + k];
-                xrow += NO;
-            }
+            run_load<T, KI>(D.xin, xoff, x0[u]);
+            xoff += xstep;
         }
     };
     int nc = 0;   // next row whose multipliers differ (row 0 first)
     if constexpr (AHEAD) run_load<T, C>(stbase, off0, sg);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if constexpr (INF) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) x0[u][k] = T(0);
-        }
-        fetch(u);
-    }
+    for (int u = 0; u < U; ++u) fetch(u);
 
     if (stopped) return;   // checked here, behind the loads: one memory round trip less at the start
 
-    // Flux exchange in LDS: [2 buffers][U rows][planes][strips][WE wavefronts][64 RC cells], the cells in
-    // groups of V: group-major over the lanes where a lane holds whole groups (conflict-free 16-byte
-    // writes), plain cell order elsewhere.
+    // Flux exchange in LDS: [2 buffers][U rows][strips][NE entries][GC values], the values in groups of
+    // V: group-major over the lanes where a lane holds whole groups (conflict-free 16-byte writes),
+    // plain cell order elsewhere.
     typedef T VV __attribute__((ext_vector_type(V)));
     constexpr bool GROUPS = RC % V == 0;
-    constexpr int VW = GROUPS ? V : RC % 2 == 0 ? 2 : 1;   // cells per write
+    constexpr int VW = GROUPS ? V : RC % 2 == 0 ? 2 : 1;   // values per write
+    constexpr int LE = 64 / EG;                            // lanes of an entry
     typedef T VX __attribute__((ext_vector_type(VW)));
-    constexpr int ROW = NPL * W * WV;
+    constexpr int ROW = SPLIT * NE * GC;
     T* const hand = lds + 2 * U * ROW;       // x-face values between strips: [2 buffers][U rows][WE][K]
+    const int mine = (strip * NE + (RAW ? entry * EG + g : entry)) * GC + (GROUPS ? (lane % LE) * V : pos * C + (RAW ? 0 : g * RC));
     if (!live)   // a wavefront without ordinates adds zeros
-        for (int i = lane; i < 2 * U * NPL * WV; i += 64) lds[(i / WV) * (W * WV) + (strip * WE + entry) * WV + i % WV] = T(0);
-    // The flux sum in chunks of V consecutive cells of a (row, plane), one per lane and piece: this
-    // wavefront's piece n is e = n W + wave (coalesced stores).  A chunk's place in the plane is a
-    // fixed byte offset from the batch's lowest row.
-    constexpr int CPR = SPLIT * WV / V;              // chunks per row and plane
-    constexpr int CHUNKS = U * NPL * CPR;
+        for (int i = lane; i < 2 * U * EG * GC; i += 64)
+            lds[i / (EG * GC) * ROW + (strip * NE + entry * EG) * GC + i % (EG * GC)] = T(0);
+    // weights of the entries in each plane (RAW; zero for those without ordinates)
+    T wt[RAW ? NPL : 1][RAW ? NE : 1];
+    if constexpr (RAW) {
+        const auto to = scalar_ptr(D.ords);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int o = min(e, D.nw * EG - 1);
+            const double we = e < D.nw * EG ? to[o].w : 0.0;
+            wt[0][e] = to_T<T>(we);
+            if constexpr (MODE == 1) {
+                wt[1][e] = to_T<T>(we * to[o].m1);
+                wt[2][e] = to_T<T>(we * to[o].m2);
+                wt[3][e] = to_T<T>(we * to[o].m3);
+            }
+        }
+    }
+    // The flux sum in chunks of V consecutive cells of a row, one per lane and piece: this wavefront's
+    // piece n is e = n W + wave (coalesced stores).  A chunk's place in the plane is a fixed byte
+    // offset from the batch's lowest row.
+    constexpr int CPR = SPLIT * GC / V;              // chunks per row
+    constexpr int CHUNKS = U * CPR;
     constexpr int PER = (CHUNKS + 64 * W - 1) / (64 * W);
     constexpr bool EVEN = CHUNKS % (64 * W) == 0;
     // a lone wavefront per SIMD finishes a batch's sum after the next batch's first row, behind which
     // its LDS reads return; elsewhere the other wavefronts hide them
-    constexpr bool DEFER = K == 1 && SPLIT == 1 && PER * W * V * sizeof(T) <= 512;
+    constexpr bool DEFER = RAW && PER * NE * V * sizeof(T) <= 512;
     int pu[PER], pl[PER];          // row of the chunk (from the first strip's batch), place in the exchange buffer
     uint32_t po[PER];              // byte offset of its first cell
     int pc[PER];                   // first cell (past nx: nothing to store)
 #pragma unroll
     for (int n = 0; n < PER; ++n) {
         const int e = (n * W + wave) * 64 + lane;
-        const int rp = min(e, CHUNKS - 1) / CPR, x = (e % CPR) * V;
-        const int q = rp % NPL, u = rp / NPL, sp = x / WV, xs = x % WV;
+        const int u = min(e, CHUNKS - 1) / CPR, x = (e % CPR) * V, sp = x / GC, xs = x % GC;
         pu[n] = u - sp * U;
         if constexpr (CPR % 64 == 0 && SPLIT == 1) pu[n] = uniform(pu[n]);
-        pc[n] = e < CHUNKS && (MODE == 0 || q < np) ? x : nx;
-        const int c = xs % C;
-        pl[n] = u * ROW + (q * W + sp * WE) * WV + (GROUPS ? (((c % RC) / V) * 64 + (c / RC) * G + xs / C) * V : xs);
+        pc[n] = e < CHUNKS ? x : nx;
+        const int c = xs % C, l = (RAW ? 0 : (c / RC) * G) + xs / C;   // the lane of the entry that holds it
+        pl[n] = u * ROW + sp * NE * GC + (GROUPS ? ((c % RC) / V * LE + l) * V : xs);
         const int up = D.ypos ? pu[n] + (SPLIT - 1) * U : U - 1 - pu[n];   // rows above the batch's lowest
-        po[n] = sizeof(T) * ((uint32_t)(up * nx + (DIR > 0 ? x : nx - 1 - min(x, nx - 1))) + (uint32_t)q * (uint32_t)D.plane);
+        po[n] = sizeof(T) * (uint32_t)(up * nx + (DIR > 0 ? x : nx - 1 - min(x, nx - 1)));
     }
     T* pbase = D.part + (D.ypos ? -(int64_t)(SPLIT - 1) * U * nx : (int64_t)(ny - U) * nx);   // lowest row of the batch
     // one finished piece: rows past the grid and cells past the row are not stored
-    auto piece_store = [&](const int n, const int jb, const VV& sum) {
+    auto piece_store = [&](const int n, const int jb, const int q, const VV& sum) {
         const bool in = pu[n] < ny - jb && (SPLIT == 1 || jb + pu[n] >= 0);
-        T* const at = (T*)((char*)pbase + po[n]);
+        T* const at = (T*)((char*)(pbase + (MODE == 1 ? q * D.plane : 0)) + po[n]);
         if (in && pc[n] + V <= nx) {
             typedef T VU __attribute__((ext_vector_type(V), aligned(sizeof(T))));
             VU out;
@@ -460,39 +482,60 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
             }
         }
     };
-    VV r[DEFER ? PER : 1][DEFER ? W : 1];
+    // the entries of a piece, in order
+    auto piece_sums = [&](const int n, const int jb, const VV (&r)[NE]) {
+        if constexpr (RAW) {
+#pragma unroll
+            for (int q = 0; q < NPL; ++q) {
+                if (q < np) {
+                    VV sum;
+#pragma unroll
+                    for (int i = 0; i < V; ++i) sum[i] = wt[q][0] * r[0][i];
+#pragma unroll
+                    for (int e = 1; e < NE; ++e)
+#pragma unroll
+                        for (int i = 0; i < V; ++i) sum[i] = fma(wt[q][e], r[e][i], sum[i]);
+                    piece_store(n, jb, q, sum);
+                }
+            }
+        }
+    };
+    VV r[DEFER ? PER : 1][DEFER ? NE : 1];
     auto sum_reads = [&](const T* buf) {
 #pragma unroll
         for (int n = 0; n < PER; ++n)
 #pragma unroll
-            for (int v = 0; v < WE; ++v) r[n][v] = *reinterpret_cast<const VV*>(buf + pl[n] + v * WV);
+            for (int e = 0; e < NE; ++e) r[n][e] = *reinterpret_cast<const VV*>(buf + pl[n] + e * GC);
     };
-    auto sum_store = [&](const int jb) {   // a fixed tree over the wavefronts
+    auto sum_store = [&](const int jb) {
+        if constexpr (DEFER) {
 #pragma unroll
-        for (int n = 0; n < PER; ++n) {
-#pragma unroll
-            for (int v = 1; v < W; v *= 2)
-#pragma unroll
-                for (int i = 0; i + v < W; i += 2 * v) r[n][i] += r[n][i + v];
-            piece_store(n, jb, r[n][0]);
+            for (int n = 0; n < PER; ++n) piece_sums(n, jb, r[n]);
         }
         pbase += U * step;
     };
-    auto sum_now = [&](const T* buf, const int jb) {   // four wavefronts at a time
+    auto sum_now = [&](const T* buf, const int jb) {
 #pragma unroll
         for (int n = 0; n < PER; ++n) {
             if (!EVEN && (n * W + wave) * 64 >= CHUNKS) continue;
             const T* src = buf + pl[n];
-            VV sum{};
+            if constexpr (RAW) {
+                VV now[NE];
 #pragma unroll
-            for (int v = 0; v < WE; v += 4) {
-                VV q[4];
+                for (int e = 0; e < NE; ++e) now[e] = *reinterpret_cast<const VV*>(src + e * GC);
+                piece_sums(n, jb, now);
+            } else {   // four wavefronts at a time
+                VV sum{};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) q[i] = v + i < WE ? *reinterpret_cast<const VV*>(src + (v + i) * WV) : VV{};
-                const VV four = (q[0] + q[1]) + (q[2] + q[3]);
-                sum = v == 0 ? four : sum + four;
+                for (int v = 0; v < NE; v += 4) {
+                    VV q[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) q[i] = v + i < NE ? *reinterpret_cast<const VV*>(src + (v + i) * GC) : VV{};
+                    const VV four = (q[0] + q[1]) + (q[2] + q[3]);
+                    sum = v == 0 ? four : sum + four;
+                }
+                piece_store(n, jb, 0, sum);
             }
-            piece_store(n, jb, sum);
         }
         pbase += U * step;
     };
@@ -539,38 +582,34 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
                         t[k][c] = fma(b[k], y[k][c], s) * rr[k][c];
                     }
                     // lane totals, the group's inflow entering its first lane
-                    if constexpr (SPLIT > 1) x[k] = pos != 0 ? T(0) : strip > 0 ? xs[u][k] : INF ? x0[INF ? u : 0][INF ? k : 0] : T(0);
-                    else x[k] = INF && pos == 0 ? x0[INF ? u : 0][INF ? k : 0] : T(0);   // the other lanes get theirs from the scan
+                    if constexpr (SPLIT > 1) x[k] = pos != 0 ? T(0) : strip > 0 ? xs[u][k] : first ? x0[INF ? u : 0][INF ? k : 0] : T(0);
+                    else x[k] = first ? x0[INF ? u : 0][INF ? k : 0] : T(0);   // the other lanes get theirs from the scan
                     T f = x[k];
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
                         if (!INF && SPLIT == 1 && c == 0) f = DD ? T(2) * t[k][0] : t[k][0];
-                        else if constexpr (DD) f = fma(T(2), fma(A[k][c], f, t[k][c]), -f);
+                        else if constexpr (DD) f = fma(X[k][c], f, T(2) * t[k][c]);
                         else f = fma(A[k][c], f, t[k][c]);
                     }
                     bt[k] = f;
                 }
                 fetch(u);
                 scan_lanes<G, K>(bt, m, x, pos);
-                T acc[NPL][C];
+                T acc[C];   // what the lane exchanges, before the sum over lane groups
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
                         const T v = fma(A[k][c], x[k], t[k][c]);
                         if constexpr (DD) {
-                            x[k] = fma(T(2), v, -x[k]);
+                            x[k] = fma(X[k][c], x[k], T(2) * t[k][c]);
                             y[k][c] = fma(T(2), v, -y[k][c]);
                         } else {
                             x[k] = v;
                             y[k][c] = v;
                         }
-                        acc[0][c] = k == 0 ? w[k] * v : fma(w[k], v, acc[0][c]);
-                        if constexpr (MODE == 1) {
-                            acc[1][c] = k == 0 ? w1[k] * v : fma(w1[k], v, acc[1][c]);
-                            acc[2][c] = k == 0 ? w2[k] * v : fma(w2[k], v, acc[2][c]);
-                            acc[3][c] = k == 0 ? w3[k] * v : fma(w3[k], v, acc[3][c]);
-                        }
+                        if constexpr (RAW) acc[c] = v;
+                        else acc[c] = k == 0 ? w[k] * v : fma(w[k], v, acc[c]);
                     }
                 }
                 if constexpr (SPLIT > 1) {   // the strip's outgoing x-face values
@@ -579,20 +618,20 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
                         for (int k = 0; k < K; ++k) hand[(((bi & 1) * U + u) * WE + entry) * K + k] = x[k];
                     }
                 }
+                T out[RC];
+                if constexpr (RAW) {
 #pragma unroll
-                for (int q = 0; q < NPL; ++q) {
-                    if (q < 3 || q < np) {
-                        T out[RC];
-                        group_sums<T, G, C>(acc[q], out);
-                        T* const mine = buf + u * ROW + (q * W + strip * WE + entry) * WV + (GROUPS ? lane * V : pos * C + g * RC);
+                    for (int c = 0; c < C; ++c) out[c] = acc[c];
+                } else {
+                    group_sums<T, G, C>(acc, out);
+                }
+                T* const to = buf + u * ROW + mine;
 #pragma unroll
-                        for (int h = 0; h < RC / VW; ++h) {
-                            VX v;
+                for (int h = 0; h < RC / VW; ++h) {
+                    VX v;
 #pragma unroll
-                            for (int e = 0; e < VW; ++e) v[e] = out[h * VW + e];
-                            *reinterpret_cast<VX*>(mine + (GROUPS ? h * 64 * V : h * VW)) = v;
-                        }
-                    }
+                    for (int e = 0; e < VW; ++e) v[e] = out[h * VW + e];
+                    *reinterpret_cast<VX*>(to + (GROUPS ? h * LE * V : h * VW)) = v;
                 }
             }
         }
@@ -629,9 +668,11 @@ __device__ __forceinline__ void scan_group(const ScanArgs& A, const __attribute_
     D.part = (T*)A.part + TK.part_off;
     D.next = A.next + TK.next_off;
     const int wv = min(wave / SPLIT, D.nw - 1);
-    const LaneDev* ords = A.ords + TK.ord_off + wv * NO;
+    D.ords = A.ords + TK.ord_off;
+    const LaneDev* ords = D.ords + wv * NO;
     // inflow tables: x-face [group][ny + padding][NO], y-face [group][NO][SPLIT G C], sweep order
-    D.xin = INF && TK.xin_off >= 0 ? (const T*)A.inflow + TK.xin_off + (int64_t)wv * (D.ny + 2 * kScanAhead) * NO : nullptr;
+    D.has_xin = INF && TK.xin_off >= 0;
+    D.xin = (const T*)A.inflow + (D.has_xin ? TK.xin_off + (int64_t)wv * (D.ny + 2 * kScanAhead) * NO : 0);
     const T* yin = INF && TK.yin_off >= 0 ? (const T*)A.inflow + TK.yin_off + (int64_t)wv * NO * (SPLIT * G * C) : nullptr;
     const int np = A.mom_r ? 4 : 3;
     if (quad == 0 || quad == 3)
@@ -655,16 +696,16 @@ template <typename T, int C, int MODE>
 constexpr int scan_ahead()
 {
     constexpr int words = C * (int)sizeof(T) / 4 * (MODE == 1 ? 3 : 1);
-    return words <= 8 ? 8 : words <= 16 ? 4 : 2;
+    return words <= 8 ? 8 : words <= 16 ? 4 : words <= 32 && MODE == 0 ? 2 : 1;
 }
 
 template <typename T, int G, int C, int W, int MODE, bool DD, bool INF>
-hipError_t launch_scan_t(const ScanArgs& a, int ntasks, hipStream_t s)
+hipError_t launch_scan_w(const ScanArgs& a, int ntasks, hipStream_t s)
 {
     constexpr int U = scan_ahead<T, C, MODE>();
     static_assert(U <= kScanAhead, "pools and tables are padded for kScanAhead rows");
     if (ntasks < 1) return hipErrorInvalidValue;
-    constexpr size_t lds = sizeof(T) * 2 * U * (MODE == 1 ? 4 : 1) * W * (size_t)(C * G);
+    constexpr size_t lds = sizeof(T) * 2 * U * W * (size_t)(C * 64);
     static_assert(lds <= 160 * 1024, "LDS");
     auto kern = scan_kernel<T, G, C, U, W, MODE, DD, INF>;
     if (lds > 64 * 1024) {
@@ -673,6 +714,12 @@ hipError_t launch_scan_t(const ScanArgs& a, int ntasks, hipStream_t s)
     }
     hipLaunchKernelGGL(kern, dim3(ntasks), dim3(64 * W), lds, s, a);
     return hipGetLastError();
+}
+
+template <typename T, int G, int C, int W, int MODE, bool DD>
+hipError_t launch_scan_t(const ScanArgs& a, int ntasks, bool inf, hipStream_t s)
+{
+    return inf ? launch_scan_w<T, G, C, W, MODE, DD, true>(a, ntasks, s) : launch_scan_w<T, G, C, W, MODE, DD, false>(a, ntasks, s);
 }
 
 }  // namespace rom

@@ -4,21 +4,22 @@
 
 namespace rom {
 
-#define ROM_SCAN_CASE(G_, C_)                                                                   \
-    if (G == G_ && C == C_)                                                                     \
-        return inf ? launch_scan_t<double, G_, C_, kScanWaves, 0, false, true>(a, ntasks, s)    \
-                   : launch_scan_t<double, G_, C_, kScanWaves, 0, false, false>(a, ntasks, s);
+#define ROM_SCAN_CASE(G_, C_, W_) \
+    if (G == G_ && C == C_ && W == W_) return launch_scan_t<double, G_, C_, W_, 0, false>(a, ntasks, inf, s);
 
-hipError_t launch_scan_f64(const ScanArgs& a, int ntasks, int G, int C, bool inf, hipStream_t s)
+hipError_t launch_scan_f64(const ScanArgs& a, int ntasks, int W, int G, int C, bool inf, hipStream_t s)
 {
-    ROM_SCAN_CASE(64, 1)
-    ROM_SCAN_CASE(64, 2)
-    ROM_SCAN_CASE(64, 3)
-    ROM_SCAN_CASE(64, 4)
-    ROM_SCAN_CASE(64, 6)
-    ROM_SCAN_CASE(64, 8)
-    ROM_SCAN_CASE(64, 16)
-    ROM_SCAN_CASE(16, 4)
+    ROM_SCAN_CASE(64, 1, 4)
+    ROM_SCAN_CASE(64, 2, 4)
+    ROM_SCAN_CASE(64, 3, 4)
+    ROM_SCAN_CASE(64, 4, 4)
+    ROM_SCAN_CASE(64, 6, 4)
+    ROM_SCAN_CASE(64, 8, 4)
+    ROM_SCAN_CASE(64, 16, 4)
+    ROM_SCAN_CASE(16, 4, 1)
+    ROM_SCAN_CASE(16, 4, 4)
+    ROM_SCAN_CASE(16, 8, 1)
+    ROM_SCAN_CASE(16, 8, 4)
     return hipErrorInvalidValue;
 }
 

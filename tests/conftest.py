@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -18,3 +19,10 @@ def orc():
     import oracle
     oracle.lib()
     return oracle
+
+
+@pytest.fixture(scope="module", autouse=True)
+def no_handles_of_other_modules():
+    """Handles that an earlier module's exception cycles still hold are closed here, not at some
+    allocation inside a test that counts device memory."""
+    gc.collect()
