@@ -295,6 +295,7 @@ struct Plan {
     Arena* arena = nullptr;                 // placement of the buffers (NULL: allocated)
     std::vector<std::vector<char>> keep;    // host sources of the arena uploads
     bool fp64 = false, dd = false, aniso = false;
+    int contract = 0;                       // kind of the dense kernels' contraction (launch_contract)
     int nmom = 1;       // 4: linear-kernel moment sweep (three source planes, four partial planes)
     int mom_r = 0;      // linear kernel normalized somewhere in the batch: form phi~ separately
     int64_t src_len = 0;  // elements of the source pool (without its padding)
@@ -390,7 +391,7 @@ struct Plan {
     char* st_ptr() const { return (char*)d_st.p + (size_t)pad * esz; }
     char* src_ptr() const { return (char*)d_src.p + (size_t)pad * esz; }
 
-    ScanArgs scan_args(int mode_all) const
+    ScanArgs scan_args(int mode_all, int ang_iso) const
     {
         ScanArgs a{};
         a.tasks = d_stasks.as<ScanTaskDev>();
@@ -402,8 +403,11 @@ struct Plan {
         a.inflow = d_inflow.p;
         a.ctl = d_ctl.as<Ctl>();
         a.sysctl = d_sysctl.as<SysCtl>();
+        a.ang = d_ang.p;
+        a.psi = d_psi.p;
         a.mode_all = mode_all;
         a.mom_r = mom_r;
+        a.ang_iso = ang_iso;
         return a;
     }
 
@@ -433,10 +437,11 @@ struct Plan {
         return a;
     }
 
-    // one sweep of every running system, with the plan's kernel
-    hipError_t launch_sweep_any(int mode_all, hipStream_t s) const
+    // one sweep of every running system, with the plan's kernel (ang_iso: see ScanArgs)
+    hipError_t launch_sweep_any(int mode_all, hipStream_t s, int ang_iso = 0) const
     {
-        if (kind == kSweepScan) return launch_scan(scan_args(mode_all), (int)stasks.size(), sW, fp64, sG, sC, nmom, dd, inflow_len > 0, s);
+        if (kind == kSweepScan)
+            return launch_scan(scan_args(mode_all, ang_iso), (int)stasks.size(), sW, fp64, sG, sC, aniso ? 0 : nmom, dd, inflow_len > 0, s);
         if (kind == ROM_SWEEP_DIAG) return launch_diag(diag_args(mode_all), grid, dNB, fp64, dR, dK, aniso, s);
         return launch_sweep(sweep_args(mode_all, 0), grid, fp64, tx, ty, dd, aniso, aniso ? (fp64 ? 1 : 2) : 0, L, nmom, s);
     }
@@ -819,6 +824,7 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     P.fp64 = o.precision == ROM_PREC_FP64;
     P.dd = o.scheme == ROM_SCHEME_DD;
     P.aniso = aniso;
+    P.contract = P.fp64 ? 2 : 0;
     P.nmom = smode == 1 ? 4 : 1;
     P.mom_r = 0;
     if (smode == 1)
@@ -830,14 +836,14 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     int maxnx = 1;
     for (auto& s : in) maxnx = std::max(maxnx, s.h->grid.nx);
     if (P.kind == kSweepScan) {
-        if (psi_out || aniso || P.arena) throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: sources from the scalar flux and its moments"};
+        if (psi_out || max_iter == 0 || P.arena) throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: source iterations"};
         P.sG = o.diag_rows;
         P.sC = o.tile_x;
         P.sW = o.band;
-        if (!scan_supported(P.fp64, P.sW, P.sG, P.sC, P.nmom, P.dd) || maxnx > (P.sW <= kScanWaves ? P.sG * P.sC : kScanMaxNx))
+        if (!scan_supported(P.fp64, P.sW, P.sG, P.sC, aniso ? 0 : P.nmom, P.dd) || maxnx > (P.sW <= kScanWaves ? P.sG * P.sC : kScanMaxNx))
             throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: shape"};
         for (auto& s : in)  // the kernel's byte offsets within a system are 32-bit
-            if ((s.h->cells * P.nmom + (4 * kScanAhead + 1) * (int64_t)s.h->grid.nx) * P.esz >= (int64_t)1 << 32)
+            if ((s.h->cells * (aniso ? 4 : P.nmom) + (4 * kScanAhead + 1) * (int64_t)s.h->grid.nx) * P.esz >= (int64_t)1 << 32)
                 throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: grid too large"};
         P.pad = std::max<int64_t>(kPoolPad, 2 * kScanAhead * (int64_t)maxnx + 64);
     }
@@ -1098,7 +1104,8 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
             uo.clear();
             for (int q = 0; q < 4; ++q) {
                 const auto& list = ql[sy].idx[q];
-                // the quadrant's groups in workgroups of at most W wavefronts, evenly
+                // the quadrant's groups in workgroups of at most W wavefronts, evenly (dense kernels:
+                // full ones first, since an FP32 workgroup writes planes of four ordinates)
                 const int most = P.sW / P.scan_shape(p).strips;
                 const int nwv = ((int)list.size() + NO - 1) / NO, ngrp = (nwv + most - 1) / most;
                 int wv = 0;
@@ -1109,7 +1116,8 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
                     t.cls = scan_class(h->grid.nx);
                     t.nx = h->grid.nx;
                     t.ny = h->grid.ny;
-                    t.nw = nwv / ngrp + (gi < nwv % ngrp ? 1 : 0);
+                    t.nw = aniso ? std::min(most, nwv - gi * most) : nwv / ngrp + (gi < nwv % ngrp ? 1 : 0);
+                    t.ang_off = (int64_t)uo.size();
                     t.field_off = field_off[p];
                     t.src_off = P.sys[sy].src_off;
                     t.part_off = part_sum;
@@ -1138,8 +1146,34 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
                     ++P.nslots;
                     P.stasks.push_back(t);
                 }
+                while (aniso && uo.size() % 4 != 0) uo.push_back(-1);
             }
             P.npad_al[sy] = P.sys[sy].npad = (int)uo.size();
+        }
+        if (aniso) {   // a plane per ordinate, padded to the contraction's K step; the pools as the others
+            ang_sum = (P.pad + 63) / 64 * 64;
+            int most = 0;
+            for (int sy = 0; sy < P.nsys; ++sy) {
+                P.npad_al[sy] = P.sys[sy].npad = ((int)P.user_of[sy].size() + 31) / 32 * 32;
+                most = std::max(most, P.npad_al[sy]);
+                P.sys[sy].ang_off = ang_sum;
+                ang_sum += ang_plane(P.handles[P.sys[sy].prob]->cells) * P.npad_al[sy];
+            }
+            for (ScanTaskDev& t : P.stasks) t.ang_off = P.sys[t.sys].ang_off + t.ang_off * ang_plane((int64_t)t.nx * t.ny);
+            ang_sum += P.pad;
+            // the widest tile that still gives each CU two blocks (16384 cells x 256 ordinates: 7.5 us on
+            // 128-wide tiles, 10 on 256; x 128: 4.7 on 64, 5.6 on 128)
+            P.contract = kContractPlanesF64;
+            for (const int bn : {256, 128, 64}) {
+                int64_t blocks = 0;
+                for (int sy = 0; sy < P.nsys; ++sy)
+                    blocks += (P.handles[P.sys[sy].prob]->cells + 127) / 128 * ((P.npad_al[sy] + bn - 1) / bn);
+                if (P.fp64 || (bn > 64 && (most < bn || blocks < 2 * device_cus()))) continue;
+                P.contract = bn == 256 ? kContractPlanes256 : bn == 128 ? kContractPlanes128 : kContractPlanes64;
+                break;
+            }
+            // sources and fluxes beyond the 256 MB cache
+            if (!P.fp64 && ang_sum * 6 > ((int64_t)256 << 20)) P.contract += kContractStream;
         }
         // the longest tasks first, so no large one is left for the end of a launch
         std::stable_sort(P.stasks.begin(), P.stasks.end(), [](const ScanTaskDev& x, const ScanTaskDev& y) {
@@ -1348,6 +1382,7 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     if (aniso) {
         take(P, P.d_ang, std::max<int64_t>(ang_sum, 1) * P.esz);
         take(P, P.d_psi, std::max<int64_t>(ang_sum, 1) * (P.fp64 ? 8 : 2));
+        if (P.kind == kSweepScan) zero(P, P.d_psi.p, ang_sum * (P.fp64 ? 8 : 2));   // padded ordinates stay so
     }
 }
 
@@ -1420,6 +1455,7 @@ void build_kernel_matrices(Plan& P, const std::vector<SysInput>& in, hipStream_t
     a.nsys = P.nsys;
     a.fp64 = P.fp64 ? 1 : 0;
     a.max_al = max_al;
+    a.piece = P.contract < kContractPlanes64 ? 0 : P.fp64 ? 2 : 8;
     HIPCHK(launch_kernel_matrix(a, s));
 }
 
@@ -1533,6 +1569,7 @@ bool refresh_ordinates(Plan& P, const std::vector<SysInput>& in, hipStream_t s)
                     uo.push_back(u);
                     fill_lane(ld, h, in[k], u, inv_r);
                 }
+                while (P.aniso && uo.size() % 4 != 0) uo.push_back(-1);
             }
             if (uo.size() != before) throw Fail{ROM_E_STATE, "ordinate layout changed"};
             P.sys_n[k] = in[k].n;
@@ -1540,6 +1577,7 @@ bool refresh_ordinates(Plan& P, const std::vector<SysInput>& in, hipStream_t s)
         }
         rewrite(P.d_lanes, P.lanes, s);
         refresh_g(P, in, s);
+        if (P.aniso) build_kernel_matrices(P, in, s);
         if (P.inflow_len > 0) {
             P.h_inflow = scan_inflow_table(P, in);
             if (P.fp64) {
@@ -1602,6 +1640,7 @@ ContractArgs contract_args(const Plan& P, int k)
     c.q = (const char*)P.d_q.p + P.probs[sd.prob].field_off * P.esz;
     c.out = (char*)P.d_ang.p + sd.ang_off * P.esz;
     c.M = (int)P.handles[sd.prob]->cells;
+    c.ld = (int)ang_plane(c.M);
     c.N = c.K = P.npad_al[k];
     c.sys_index = k;
     c.sysctl = P.d_sysctl.as<SysCtl>();
@@ -1615,7 +1654,7 @@ ContractArgs contract_args(const Plan& P, int k)
 void build_contract_batch(Plan& P)
 {
     if (!P.aniso || P.nsys < 2) return;
-    const int kind = P.fp64 ? 2 : 0;
+    const int kind = P.contract;
     std::vector<ContractArgs> items(P.nsys);
     std::vector<int2> map;
     for (int k = 0; k < P.nsys; ++k) {
@@ -1629,18 +1668,21 @@ void build_contract_batch(Plan& P)
     P.cmap_blocks = (int)map.size();
 }
 
-void enqueue_iteration(Plan& P, hipStream_t s, double tol)
+// first: the first iteration, with phi = 0.  The row-scan sweep then takes q itself for every ordinate's
+// source (256^2, 1024 ordinates: the cleared angular flux and its contraction are 0.2 ms of a solve).
+void enqueue_iteration(Plan& P, hipStream_t s, double tol, bool first)
 {
-    if (P.aniso) {
+    const bool iso = first && P.aniso && P.kind == kSweepScan;
+    if (P.aniso && !iso) {
         // the contraction's last block stamps the start of the sweep's timing (not the combine's end)
         Ctl* const ctl = P.d_ctl.as<Ctl>();
         if (P.cmap_blocks > 0) {
-            HIPCHK(launch_contract_batch(P.d_citems.as<ContractArgs>(), P.d_cmap.as<int2>(), P.cmap_blocks, P.fp64 ? 2 : 0, s, ctl));
+            HIPCHK(launch_contract_batch(P.d_citems.as<ContractArgs>(), P.d_cmap.as<int2>(), P.cmap_blocks, P.contract, s, ctl));
         } else {
-            for (int k = 0; k < P.nsys; ++k) HIPCHK(launch_contract(contract_args(P, k), P.fp64 ? 2 : 0, s, ctl));
+            for (int k = 0; k < P.nsys; ++k) HIPCHK(launch_contract(contract_args(P, k), P.contract, s, ctl));
         }
     }
-    HIPCHK(P.launch_sweep_any(0, s));
+    HIPCHK(P.launch_sweep_any(0, s, iso ? 1 : 0));
     const CombineArgs ca = P.combine_args(0, tol);
     HIPCHK(launch_combine(ca, (int)P.cblocks.size(), P.fp64, s));
 }
@@ -1686,7 +1728,7 @@ SolveResult run_si(Plan& P, hipStream_t s, const rom_si_opts& o)
             psi_total = std::max<int64_t>(psi_total, P.sys[k].ang_off + P.handles[P.sys[k].prob]->cells * (int64_t)P.npad_al[k]);
     auto enqueue_initial_state = [&]() {
         if (P.nmom == 4) HIPCHK(launch_fill(P.src_ptr(), P.src_len, P.fp64, 0.0, s));  // S1 = S2 = 0
-        if (P.aniso) {
+        if (P.aniso && P.kind != kSweepScan) {
             if (P.fp64) HIPCHK(launch_fill(P.d_psi.p, psi_total, true, 0.0, s));
             else HIPCHK(launch_fill(P.d_psi.p, (psi_total + 1) / 2, false, 0.0, s));  // BF16 zeros are float zeros
         }
@@ -1700,7 +1742,7 @@ SolveResult run_si(Plan& P, hipStream_t s, const rom_si_opts& o)
             // replay's last combine; after the initial state it is timed from its first ticket claim
             if (with_initial_state) enqueue_initial_state();
             else HIPCHK(launch_mark(P.d_ctl.as<Ctl>(), s));
-            for (int k = 0; k < K; ++k) enqueue_iteration(P, s, tol);
+            for (int k = 0; k < K; ++k) enqueue_iteration(P, s, tol, with_initial_state && k == 0);
         } catch (...) {
             hipGraph_t gg = nullptr;
             (void)hipStreamEndCapture(s, &gg);
@@ -1767,7 +1809,7 @@ SolveResult run_si(Plan& P, hipStream_t s, const rom_si_opts& o)
     r.kind = P.kind;
     if (P.kind == kSweepScan) {
         // reported among the row-lane sweeps, or the strip sweeps where those do not apply
-        r.kind = P.nmom == 1 && !P.dd ? ROM_SWEEP_DIAG : ROM_SWEEP_STRIP;
+        r.kind = P.nmom == 1 && !P.dd && !(P.aniso && P.fp64) ? ROM_SWEEP_DIAG : ROM_SWEEP_STRIP;
         r.tx = P.scan_shape(0).K;
         r.ty = P.scan_shape(0).G == 16 ? 16 : 64;
         r.band = P.sW;
@@ -2276,8 +2318,8 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
     int C = (maxnx + 63) / 64;
     while (C <= 16 && !scan_supported(fp64, 4, 64, C, mom, dd)) ++C;
     if (C <= 16) c.push_back({kSweepScan, C, 0, 4, 64, 1});
-    if (maxnx <= 128) c.push_back({kSweepScan, maxnx <= 64 ? 4 : 8, 0, maxn <= 16 ? 1 : 4, 16, 1});
-    if (scan_supported(fp64, 8, 0, 0, mom, dd) && maxnx <= kScanMaxNx) {
+    if (maxnx <= (mom == 0 ? 64 : 128)) c.push_back({kSweepScan, maxnx <= 64 ? 4 : 8, 0, maxn <= 16 && mom != 0 ? 1 : 4, 16, 1});
+    if (mom != 0 && scan_supported(fp64, 8, 0, 0, mom, dd) && maxnx <= kScanMaxNx) {
         c.push_back({kSweepScan, 0, 0, 8, 0, 0});
         c.push_back({kSweepScan, 0, 0, 16, 0, 0});
     }
@@ -2302,9 +2344,9 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 //     workgroups are full (512^2, 64 samples of 128: 467 us against 550; 24 uneven problems: 784 / 512).
 bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode, TuneChoice& pick)
 {
-    if (o.sweep != ROM_SWEEP_AUTO || smode == 2) return false;
+    if (o.sweep != ROM_SWEEP_AUTO || (smode == 2 && o.scheme == ROM_SCHEME_DD)) return false;
     const bool fp64 = o.precision == ROM_PREC_FP64, dd = o.scheme == ROM_SCHEME_DD;
-    const int mom = smode == 1 ? 4 : 1;
+    const int mom = smode == 1 ? 4 : smode == 2 ? 0 : 1;
     int maxnx = 0, maxny = 0, maxn = 0;
     int64_t ords = 0, rows = 0, changes = 0, groups = 0, space = 0;
     for (auto& s : in) {
@@ -2339,6 +2381,13 @@ bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode,
         return false;
     };
     if (mom == 4 || dd) return maxnx <= 512 && take(4, maxnx <= 64 && ords >= 4096 ? 16 : 64);
+    // dense kernels: 64-lane groups, whose source planes are read in long runs (256^2 x 1024, sweep,
+    // contraction and combine: 291 us against 486 on the row-lane kernel; 8 samples of 64^2 x 64: 26 / 54;
+    // FP64 96 x 80: 51 / 331 on the strip kernel)
+    if (mom == 0) {
+        pick = c[0];
+        return maxnx <= 512 && changes * 4 <= rows;
+    }
     if (maxnx > 64 && changes * 4 > rows) return false;
     if (maxnx > 512 && ords < 1024 && maxny > 128) return false;
     const bool sixteen = space > 0 && groups * 10 >= space * 9;

@@ -21,6 +21,16 @@ __device__ __forceinline__ int64_t uniform64(int64_t x)
     return ((int64_t)hi << 32) | (unsigned)lo;
 }
 
+// Two floats as packed BF16 (low half x), rounded to nearest even: one v_cvt_pk_bf16_f32 on gfx950.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pack(float x, float y)
+{
+    bf16x2_t v;
+    v.x = (__bf16)x;
+    v.y = (__bf16)y;
+    return __builtin_bit_cast(uint32_t, v);
+}
+
 // Strip-edge hand-off between wavefronts that may sit on different XCDs.  The edge words
 // themselves are written and read with device-scope (agent) relaxed atomic accesses, which the
 // hardware keeps coherent across the per-XCD L2 caches word by word; the producer then waits for

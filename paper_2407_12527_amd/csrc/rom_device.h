@@ -121,6 +121,10 @@ __host__ __device__ inline ScanShape scan_class_shape(int cls)
     return shape[cls];
 }
 
+// Cells from one plane of an ordinate to the next (dense kernels on the row-scan sweep): whole 128-byte
+// lines, an odd number of them, so planes of 2^k cells do not share their memory channels.
+__host__ __device__ inline int64_t ang_plane(int64_t cells) { return ((cells + 31) / 32 | 1) * 32; }
+
 struct ScanTaskDev {
     int32_t sys, quad;
     int32_t nx, ny;
@@ -133,6 +137,8 @@ struct ScanTaskDev {
     int64_t ord_off;            // first of its [nw][NO] lane-table entries
     int64_t xin_off;            // inflow on the entry x-face [nw][ny + 2 kScanAhead][NO], rows in sweep order; -1 vacuum
     int64_t yin_off;            // inflow on the entry y-face [nw][NO][strips G C], columns in sweep order; -1 vacuum
+    int64_t ang_off;            // dense kernels: its first ordinate's plane in the source and angular-flux pools
+                                // (elements; a multiple of four ordinates in)
 };
 
 // Per-system convergence state, written only by the combine step.

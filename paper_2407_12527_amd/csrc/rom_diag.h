@@ -187,16 +187,6 @@ struct DiagTask {
     int ord0;            // the task's first ordinate
 };
 
-// Two floats as packed BF16 (low half x), rounded to nearest even: one v_cvt_pk_bf16_f32 on gfx950.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t bf16_pack(float x, float y)
-{
-    bf16x2_t v;
-    v.x = (__bf16)x;
-    v.y = (__bf16)y;
-    return __builtin_bit_cast(uint32_t, v);
-}
-
 // U consecutive values at p (16-byte aligned) as 16-byte LDS or global accesses.
 template <typename T, int U>
 __device__ __forceinline__ void load_run(const T* p, T (&v)[U])

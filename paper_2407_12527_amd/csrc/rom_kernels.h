@@ -68,10 +68,14 @@ struct ScanArgs {
     const void* src;           // source pool (T)
     void* part;                // partial scalar-flux pool (T)
     const void* inflow;        // unweighted boundary inflow pool (T)
+    const void* ang;           // dense kernels: sources, a plane per ordinate (T)
+    void* psi;                 // dense kernels: weighted angular fluxes, planes of four ordinates (BF16) or of one (FP64)
     Ctl* ctl;
     SysCtl* sysctl;
     int32_t mode_all;
     int32_t mom_r;             // linear kernel: 1 = also form the 1/r-weighted density (plane 3)
+    int32_t ang_iso;           // dense kernels: 1 = every ordinate's source is `src`
+    int32_t pad;
 };
 
 struct CombineArgs {
@@ -131,7 +135,7 @@ struct ContractArgs {
     int32_t blocked;           // BF16 kernel: 1 = A and out in ordinate blocks of 16,
                                // [K / 16][M][16] and [N / 16][M][16] (the row-lane sweep's
                                // layout); 0 = row-major [M][K] and [M][N]
-    int32_t pad;
+    int32_t ld;                // planes (kinds from 3): cells from one to the next
 };
 
 // One system's transposed scattering matrix Bt[n][k] = P(u_k, u_n) / r_k: the discrete kernel of
@@ -159,7 +163,8 @@ struct KmArgs {
     double* inv_r;       // [entries]: 1 / r_k (written when norm)
     void* bt;            // matrices: BF16 bits (fp64 = 0) or doubles
     int32_t nsys, fp64;
-    int32_t max_al, pad;
+    int32_t max_al;
+    int32_t piece;       // 0: rows, Bt[n][k]; else Bt[k / piece][n][k % piece]
 };
 
 // Slab systems (Sec. 4.1): all share one problem (fields at the nn grid points), each has its own
@@ -201,8 +206,9 @@ size_t diag_lds_bytes(bool fp64, int R, int K, int nb);
 hipError_t launch_diag(const DiagArgs& a, int grid, int nb, bool fp64, int R, int K, bool ang, hipStream_t s);
 // Row-scan sweep, one workgroup per task; inf: boundary inflow tables may be present.  waves (per
 // workgroup) 1 or 4: the single-ordinate form, lane groups of G lanes with C cells each (rows of up to
-// G C cells), for isotropic sources (mom 1) and the linear kernel (mom 4), both schemes; 8 or 16: the
-// form for full GPUs (FP32 isotropic step sweeps, every task in its scan_class shape).
+// G C cells), for isotropic sources (mom 1) and the linear kernel (mom 4), both schemes, and for dense
+// kernels' per-ordinate sources (mom 0, step scheme, 4 wavefronts); 8 or 16: the form for full GPUs (FP32 isotropic
+// step sweeps, every task in its scan_class shape).
 bool scan_supported(bool fp64, int waves, int G, int C, int mom, bool dd);
 hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int G, int C, int mom, bool dd, bool inf, hipStream_t s);
 hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStream_t s);
@@ -219,7 +225,11 @@ hipError_t launch_init_state(const SystemDev* sys, const ProblemDev* probs, int 
                              hipStream_t s);
 hipError_t launch_moments(const MomentsArgs& a, bool fp64, hipStream_t s);
 hipError_t launch_finish_var(const double* m2, double* var, int64_t cells, int64_t t, hipStream_t s);
-// kind 0 bf16 MFMA, 1 fp32, 2 fp64; ctl (may be NULL): the kernel clears ctl->t_mark (the next
+// The dense kernels' contraction on the row-scan sweep's planes: BF16 tiles of that many ordinates, FP64;
+// BF16 with kContractStream added: the sources are stored past the caches.
+constexpr int kContractPlanes64 = 3, kContractPlanes128 = 4, kContractPlanes256 = 5, kContractPlanesF64 = 6;
+constexpr int kContractStream = 8;
+// kind 0 bf16 MFMA, 1 fp32, 2 fp64, from 3 the above; ctl (may be NULL): the kernel clears ctl->t_mark (the next
 // sweep is then timed from its first ticket claim)
 hipError_t launch_contract(const ContractArgs& a, int kind, hipStream_t s, Ctl* ctl = nullptr);
 // Blocks of one contraction (-1: shape not supported by the kind); several contractions in one
@@ -227,6 +237,9 @@ hipError_t launch_contract(const ContractArgs& a, int kind, hipStream_t s, Ctl* 
 int contract_blocks(const ContractArgs& a, int kind);
 hipError_t launch_contract_batch(const ContractArgs* items, const int2* map, int nblocks, int kind, hipStream_t s,
                                  Ctl* ctl = nullptr);
+int planes_blocks(const ContractArgs& a, int kind);
+hipError_t launch_planes(const ContractArgs& a, int kind, hipStream_t s, Ctl* ctl);
+hipError_t launch_planes_batch(const ContractArgs* items, const int2* map, int nblocks, int kind, hipStream_t s, Ctl* ctl);
 hipError_t launch_cast_bf16(const float* in, void* out, int64_t n, hipStream_t s);
 // Kernel matrices of every system of a plan (row sums first when a system is normalized).
 hipError_t launch_kernel_matrix(const KmArgs& a, hipStream_t s);

@@ -1009,21 +1009,22 @@ __global__ void __launch_bounds__(256) kernel_rowsum_kernel(KmArgs A)
 }
 
 // Bt[n][k] = P(u_k, u_n) / r_k over the whole [al][al] matrix (zero where n or k is padding):
-// a block writes 4 rows n, threads along k (contiguous stores).
+// a block writes 4 rows n, threads along k (contiguous stores; by pieces: those of 4 rows).
 __global__ void __launch_bounds__(256) kernel_fill_kernel(KmArgs A)
 {
     const KmSys S = A.sys[blockIdx.y];
     const int n0 = blockIdx.x * 4;
     if (n0 >= S.al) return;
+    const int run = A.piece > 0 ? A.piece : S.al;   // consecutive entries of a row
     for (int e = threadIdx.x; e < 4 * S.al; e += 256) {
-        const int n = n0 + e / S.al, k = e % S.al;
-        if (n >= S.al) break;
+        const int n = n0 + e / run % 4, k = e / (4 * run) * run + e % run;
+        if (n >= S.al) continue;
         double v = 0.0;
         if (n < S.npad && k < S.npad && A.uidx[S.ord_off + n] >= 0 && A.uidx[S.ord_off + k] >= 0) {
             v = km_value(A, S, k, n);
             if (S.norm) v *= A.inv_r[S.ord_off + k];
         }
-        const int64_t idx = S.pt_off + (int64_t)n * S.al + k;
+        const int64_t idx = S.pt_off + (A.piece > 0 ? ((int64_t)(k / run) * S.al + n) * run + k % run : (int64_t)n * S.al + k);
         if (A.fp64) {
             static_cast<double*>(A.bt)[idx] = v;
         } else {
@@ -1104,12 +1105,17 @@ hipError_t launch_diag(const DiagArgs& a, int grid, int nb, bool fp64, int R, in
 hipError_t launch_scan_f32(const ScanArgs&, int, int, int, int, bool, hipStream_t);
 hipError_t launch_scan_f64(const ScanArgs&, int, int, int, int, bool, hipStream_t);
 hipError_t launch_scan_f32_many(const ScanArgs&, int, int, bool, hipStream_t);
+hipError_t launch_scan_ang_f32(const ScanArgs&, int, int, int, bool, hipStream_t);
+hipError_t launch_scan_ang_f64(const ScanArgs&, int, int, int, bool, hipStream_t);
 hipError_t launch_scan_lin_f32(const ScanArgs&, int, int, int, int, int, bool, bool, hipStream_t);
 hipError_t launch_scan_lin_f64(const ScanArgs&, int, int, int, int, int, bool, bool, hipStream_t);
 
 bool scan_supported(bool fp64, int waves, int G, int C, int mom, bool dd)
 {
     const bool plain = mom == 1 && !dd;
+    if (mom == 0)
+        return !dd && waves == 4 &&
+               ((G == 16 && C == 4) || (G == 64 && (C == 1 || C == 2 || C == 3 || C == 4 || C == 6 || C == 8)));
     if (waves == 8 || waves == 16) return plain && !fp64;
     if (waves != 1 && waves != 4) return false;
     if (G == 16) return C == 4 || C == 8;
@@ -1121,7 +1127,8 @@ bool scan_supported(bool fp64, int waves, int G, int C, int mom, bool dd)
 hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int G, int C, int mom, bool dd, bool inf, hipStream_t s)
 {
     if (!scan_supported(fp64, waves, G, C, mom, dd)) return hipErrorInvalidValue;
-    if (waves > 4) return launch_scan_f32_many(a, ntasks, waves, inf, s);
+    if (waves > 4 && mom != 0) return launch_scan_f32_many(a, ntasks, waves, inf, s);
+    if (mom == 0) return fp64 ? launch_scan_ang_f64(a, ntasks, G, C, inf, s) : launch_scan_ang_f32(a, ntasks, G, C, inf, s);
     if (mom == 4 || dd)
         return fp64 ? launch_scan_lin_f64(a, ntasks, waves, G, C, mom, dd, inf, s)
                     : launch_scan_lin_f32(a, ntasks, waves, G, C, mom, dd, inf, s);
@@ -1298,6 +1305,7 @@ static bool contract_big_tiles()
 
 hipError_t launch_contract(const ContractArgs& a, int kind, hipStream_t s, Ctl* ctl)
 {
+    if (kind >= kContractPlanes64) return launch_planes(a, kind, s, ctl);
     if (kind == 0) {
         if (a.N % GN != 0 || a.K % GK != 0) return hipErrorInvalidValue;
         if (a.N >= 2 * GN && contract_big_tiles()) {
@@ -1322,6 +1330,7 @@ hipError_t launch_contract(const ContractArgs& a, int kind, hipStream_t s, Ctl* 
 
 int contract_blocks(const ContractArgs& a, int kind)
 {
+    if (kind >= kContractPlanes64) return planes_blocks(a, kind);
     if (kind == 0) return (a.N % GN != 0 || a.K % GK != 0) ? -1 : ((a.M + GM - 1) / GM) * (a.N / GN);
     return ((a.M + 63) / 64) * ((a.N + 63) / 64);
 }
@@ -1330,6 +1339,7 @@ hipError_t launch_contract_batch(const ContractArgs* items, const int2* map, int
                                  Ctl* ctl)
 {
     if (nblocks < 1) return hipErrorInvalidValue;
+    if (kind >= kContractPlanes64) return launch_planes_batch(items, map, nblocks, kind, s, ctl);
     if (kind == 0) hipLaunchKernelGGL(contract_bf16_batch_kernel, dim3(nblocks), dim3(256), 0, s, items, map, ctl);
     else if (kind == 1) hipLaunchKernelGGL(contract_plain_batch_kernel<float>, dim3(nblocks), dim3(256), 0, s, items, map, ctl);
     else hipLaunchKernelGGL(contract_plain_batch_kernel<double>, dim3(nblocks), dim3(256), 0, s, items, map, ctl);

@@ -25,6 +25,12 @@
 // every moment plane of the linear kernel from one exchange; with several, their weighted sum, over
 // the lane groups too by permlane swaps.  Source rows are loaded U rows ahead.  Lanes past the row's
 // end compute on clamped addresses; nothing flows back from them.
+//
+// Dense kernels (MODE 2) keep a plane of cells per ordinate, so a wavefront's source rows are as
+// contiguous as an isotropic source's; the weighted angular flux leaves from the exchange, where all of a
+// workgroup's ordinates of a cell meet.  Bound by memory: 256^2, 1024 ordinates, FP32, reads 256 MB and
+// writes 192 MB in 84 us (5.3 TB/s; the row-lane sweep on ordinate blocks took 293 us, eight wavefronts
+// per workgroup, on half the CUs, 128 us); FP64 96 x 80, 20 us (strip sweep 232).
 #pragma once
 #include "rom_common.h"
 
@@ -286,6 +292,10 @@ struct ScanTask {
     const T* S;           // source of the system (same padding); linear kernel: three planes
     T* part;              // partial-flux slot (linear kernel: consecutive planes)
     const int32_t* next;  // per sweep-order row: the next row whose sigma_t differs from the row before it
+    int64_t sstride;      // dense kernels: elements between the source planes of a wavefront's lane groups
+    char* psi;            // dense kernels: the task's weighted angular flux, planes of four ordinates in BF16
+                          // (FP32 sweeps) or of one in FP64, 8 bytes per cell
+    int64_t ld;           // dense kernels: cells from one plane to the next
     const LaneDev* ords;  // the task's ordinates
     const T* xin;         // entry x-face inflow [ny + padding][NO] of this wavefront's ordinates
     bool has_xin;         // vacuum without (xin then holds NO other values)
@@ -300,7 +310,8 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 // One task: the rows of the grid in sweep order, for this wavefront's ordinates.
-//   MODE 0: isotropic source; 1: linear kernel (three source planes, np = 3 or 4 moment planes)
+//   MODE 0: isotropic source; 1: linear kernel (three source planes, np = 3 or 4 moment planes);
+//   2: dense kernels (a source plane per ordinate, and the weighted angular flux written back)
 //   INF: boundary inflow tables may be present
 //   SPLIT = 2 (G = 64): a row is two strips of 64 C cells, one wavefront each.  The second strip's
 //   wavefront works one batch of rows behind the first's, whose outgoing x-face values it takes from
@@ -322,7 +333,8 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
     constexpr int KI = INF ? K : 1;
     constexpr int WE = W / SPLIT;            // wavefronts that share a strip
     constexpr int NE = WE * EG;              // entries summed per strip
-    static_assert(MODE == 0 || RAW, "moment planes are formed from the exchanged psi");
+    static_assert(MODE == 0 || RAW, "moment planes and angular fluxes are formed from the exchanged psi");
+    static_assert(MODE != 2 || sizeof(T) == 8 || NE % 4 == 0, "BF16 angular fluxes are kept in planes of four ordinates");
     static_assert(SPLIT == 1 || (G == 64 && W % SPLIT == 0), "strips are whole wavefronts");
     const int np = MODE == 1 ? np_ : 1;      // moment planes formed
     const int lane = threadIdx.x & (kWave - 1);
@@ -390,7 +402,7 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
     uint32_t xoff = sizeof(T) * (uint32_t)(g * K);
     if constexpr (INF) asm volatile("" : "+v"(xoff));
     const uint32_t xstep = D.has_xin ? sizeof(T) * NO : 0;
-    uint32_t off = off0;
+    uint32_t off = off0 + (MODE == 2 ? (uint32_t)(sizeof(T) * g * D.sstride) : 0);
     auto fetch = [&](const int u) {
 #pragma unroll
         for (int q = 0; q < NSRC; ++q) run_load<T, C>(sbase + q * D.plane, off, S[u][q]);
@@ -482,8 +494,47 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
             }
         }
     };
+    // a finished piece's weighted angular flux: the cells of a plane contiguous
+    auto piece_psi = [&](const int n, const int jb, const VV (&r)[NE]) {
+        constexpr int PL = sizeof(T) == 8 ? 1 : 4;   // ordinates of a plane
+        constexpr int PW = 2;                        // 4-byte words per cell
+        typedef uint32_t UP __attribute__((ext_vector_type(PW), aligned(8)));
+        const bool in = pu[n] < ny - jb;
+        char* at = D.psi + (pbase - D.part) * (4 * PW) + (int64_t)(po[n] * (4 * PW / sizeof(T)));
+#pragma unroll
+        for (int p = 0; p < NE / PL; ++p) {
+            if (p * PL < D.nw * EG) {   // uniform
+                UP v[V];
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    if constexpr (sizeof(T) == 8) {
+                        v[i] = __builtin_bit_cast(UP, wt[0][p] * r[p][i]);
+                    } else {
+#pragma unroll
+                        for (int h = 0; h < PW; ++h)
+                            v[i][h] = bf16_pack(wt[0][p * PL + 2 * h] * r[p * PL + 2 * h][i],
+                                                wt[0][p * PL + 2 * h + 1] * r[p * PL + 2 * h + 1][i]);
+                    }
+                }
+                if (in && pc[n] + V <= nx) {
+                    UP* const to = (UP*)at - (DIR > 0 ? 0 : V - 1);
+#pragma unroll
+                    for (int i = 0; i < V; ++i) to[i] = v[DIR > 0 ? i : V - 1 - i];
+                }
+                if (__builtin_expect(nx % V != 0, 0)) {   // uniform
+                    if (in && pc[n] < nx && pc[n] + V > nx) {
+#pragma unroll
+                        for (int i = 0; i + 1 < V; ++i)
+                            if (pc[n] + i < nx) ((UP*)at)[DIR * i] = v[i];
+                    }
+                }
+            }
+            at += D.ld * (4 * PW);
+        }
+    };
     // the entries of a piece, in order
     auto piece_sums = [&](const int n, const int jb, const VV (&r)[NE]) {
+        if constexpr (MODE == 2) piece_psi(n, jb, r);
         if constexpr (RAW) {
 #pragma unroll
             for (int q = 0; q < NPL; ++q) {
@@ -665,6 +716,13 @@ __device__ __forceinline__ void scan_group(const ScanArgs& A, const __attribute_
     D.plane = (int64_t)D.nx * D.ny;
     D.st = (const T*)A.sigma_t + TK.field_off;
     D.S = (const T*)A.src + TK.src_off;
+    if constexpr (MODE == 2) {
+        // the first iteration's source is the same for every ordinate
+        D.ld = ang_plane(D.plane);
+        D.sstride = A.ang_iso ? 0 : D.ld;
+        if (!A.ang_iso) D.S = (const T*)A.ang + TK.ang_off + min(wave / SPLIT, TK.nw - 1) * NO * D.ld;
+        D.psi = (char*)A.psi + TK.ang_off * (sizeof(T) == 8 ? 8 : 2);
+    }
     D.part = (T*)A.part + TK.part_off;
     D.next = A.next + TK.next_off;
     const int wv = min(wave / SPLIT, D.nw - 1);
@@ -696,7 +754,7 @@ template <typename T, int C, int MODE>
 constexpr int scan_ahead()
 {
     constexpr int words = C * (int)sizeof(T) / 4 * (MODE == 1 ? 3 : 1);
-    return words <= 8 ? 8 : words <= 16 ? 4 : words <= 32 && MODE == 0 ? 2 : 1;
+    return words <= 8 ? 8 : words <= 16 ? 4 : words <= 32 && MODE != 1 ? 2 : 1;
 }
 
 template <typename T, int G, int C, int W, int MODE, bool DD, bool INF>

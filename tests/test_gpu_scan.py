@@ -173,3 +173,55 @@ def test_the_rule_repeats_itself(R):
             assert s.lanes == 1
             got.append(phi)
         assert np.array_equal(*got)
+
+
+# Dense kernels: a source plane per ordinate, the angular flux in planes of four (BF16) or one (FP64), the
+# contraction on those planes.  Widths at the edges of the shapes, cell counts that end inside a
+# 16-byte store and a 128-byte line, ordinates that leave part of a plane and of a K step; 300 ordinates
+# run past one 256-wide tile.  A caller's unsymmetric kernel pins the contraction's orientation.  The
+# bars of the other dense-kernel tests: 2e-3 with the BF16 contraction, 1e-11 in FP64.
+@pytest.mark.parametrize("nx,ny,n,kind,inflow", [
+    (1, 1, 1, "hg", False), (3, 5, 7, "dense", True), (63, 9, 33, "hg", True), (64, 31, 12, "dense", False),
+    (65, 17, 70, "dense", True), (129, 8, 40, "hg", False), (200, 16, 300, "dense", True), (257, 7, 20, "dense", False),
+    (385, 5, 9, "hg", True), (512, 6, 30, "dense", False)])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_dense_kernels(R, orc, monkeypatch, nx, ny, n, kind, inflow, prec):
+    rng = np.random.default_rng([nx, ny, n])
+    st, ss, q = problem(rng, nx, ny, "bands")
+    infl = {f: rng.uniform(0, 1, ny if f in FACES[:2] else nx) for f in FACES} if inflow else None
+    d, w = R.generate_ordinates(R.ROM_ORD_IID_SPHERE, n, seed=nx)
+    P = rng.uniform(0.2, 1.5, (n, n))
+    W = orc.build_W(d, w, orc.SCAT_DENSE, P=P) if kind == "dense" else orc.build_W(d, w, orc.SCAT_HG, 0.7, fold=1)
+    ref = orc.source_iterate(orc.Problem(nx, ny, st, ss, q, inflow=infl), d, w, W, tol=-1, max_iter=4)["phi"]
+    fp64 = prec == "fp64"
+    for k in range(2 if nx <= 64 else 1):
+        monkeypatch.setenv("ROM_SWEEP_SCAN", str(k + 1))
+        h = R.Handle(nx, ny, st, ss, q, inflow=infl)
+        h.set_ordinates(d, w)
+        h.set_scattering(R.ROM_SCAT_DENSE if kind == "dense" else R.ROM_SCAT_HG, 0.7, P if kind == "dense" else None)
+        for check in (1, 4):   # replays of one iteration, and one replay: only the first starts from q
+            o = R.si_opts(tol=-1, max_iter=4, precision=R.ROM_PREC_FP64 if fp64 else R.ROM_PREC_FP32, iters_per_check=check)
+            phi, s, _ = h.source_iterate(o)
+            assert s.lanes == 1 and s.band == 4
+            parity.check(phi, ref, 1e-11 if fp64 else 2e-3)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_dense_batch_of_uneven_problems(R, orc, prec):
+    rng = np.random.default_rng(8)
+    hs, refs = [], []
+    for nx, ny, n in ((40, 33, 12), (130, 9, 70), (65, 20, 300)):
+        st, ss, q = problem(rng, nx, ny, "uniform")
+        d, w = R.generate_ordinates(R.ROM_ORD_IID_SPHERE, n, seed=n)
+        h = R.Handle(nx, ny, st, ss, q)
+        h.set_ordinates(d, w)
+        h.set_scattering(R.ROM_SCAT_HG, 0.6)
+        hs.append(h)
+        refs.append(orc.source_iterate(orc.Problem(nx, ny, st, ss, q), d, w, orc.build_W(d, w, orc.SCAT_HG, 0.6, fold=1), tol=-1,
+                                       max_iter=3)["phi"])
+    o = R.si_opts(tol=-1, max_iter=3, precision=R.ROM_PREC_FP64 if prec == "fp64" else R.ROM_PREC_FP32)
+    for _ in range(2):
+        phis, stats, _ = R.solve_batch(hs, o)
+        assert stats[0].lanes == 1
+        for phi, ref in zip(phis, refs):
+            parity.check(phi, ref, 1e-11 if prec == "fp64" else 2e-3)
