@@ -231,8 +231,8 @@ int rom_sweep(rom_handle* h, const double* src, int32_t src_per_ordinate, double
  * loops, harnesses that forbid hipMalloc): the sweep of rom_sweep for an isotropic source, on
  * device arrays, taking no device memory.  src_dev and phi_dev are DEVICE pointers to [cells]
  * floats (precision ROM_PREC_FP32) or doubles (ROM_PREC_FP64), src shared by all ordinates; phi
- * receives sum_l w_l psi_l with the handle's ordinates and inflow (step scheme; rom_sweep's tile
- * and band, hence its result bit for bit).  Every buffer the sweep needs lives in a 64 MiB region
+ * receives sum_l w_l psi_l with the handle's ordinates and inflow (step scheme; rom_sweep's kernel,
+ * tile and band, hence its result bit for bit).  Every buffer the sweep needs lives in a 64 MiB region
  * preallocated per GPU when the library is loaded and held until the process ends; a problem whose
  * tables, partial fluxes and strip edges do not fit is refused with ROM_E_UNSUPPORTED.  The work
  * is queued on hip_stream (NULL: the null stream) and the call returns without waiting for it.

@@ -209,7 +209,7 @@ struct rom_handle {
     double dx = 0, dy = 0;
     int64_t cells = 0;
     std::vector<double> st, ss, q;
-    int row_changes = 0;        // rows whose sigma_t differs from the row below
+    int row_changes = -1;       // rows whose sigma_t differs from the row below (-1: not counted yet)
     std::vector<double> face[4];
     // ordinates in the caller's order
     int n = 0;
@@ -836,7 +836,7 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     int maxnx = 1;
     for (auto& s : in) maxnx = std::max(maxnx, s.h->grid.nx);
     if (P.kind == kSweepScan) {
-        if (psi_out || max_iter == 0 || P.arena) throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: source iterations"};
+        if (psi_out || (aniso && max_iter == 0)) throw Fail{ROM_E_UNSUPPORTED, "row-scan sweep: no angular-flux output"};
         P.sG = o.diag_rows;
         P.sC = o.tile_x;
         P.sW = o.band;
@@ -1335,7 +1335,8 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
         }
     };
     // A single sweep placed in a caller's region takes its source and scalar flux from the
-    // caller and forms no next source: no sigma_s, q, source or flux pools of its own.
+    // caller and forms no next source: no sigma_s, q, source (but for the row-scan sweep's padded
+    // copy) or flux pools of its own.
     const bool caller_io = P.arena && max_iter == 0;
     std::vector<double> st(fsum), ss(fsum), qv(fsum);
     for (int p = 0; p < nprob; ++p) {
@@ -1363,11 +1364,11 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     }
 
     P.src_len = src_sum;
-    if (!caller_io) {
+    if (!caller_io || P.kind == kSweepScan) {
         take(P, P.d_src, (src_sum + 2 * P.pad) * P.esz);
         zero(P, P.d_src.p, (src_sum + 2 * P.pad) * P.esz);
-        take(P, P.d_phi, phi_sum * P.esz);
     }
+    if (!caller_io) take(P, P.d_phi, phi_sum * P.esz);
     take(P, P.d_part, std::max<int64_t>(part_sum, 1) * P.esz);
     take(P, P.d_edge, std::max<int64_t>(edge_sum, 1) * P.esz);
     P.prog_count = std::max(prog_sum, 1);
@@ -1896,6 +1897,9 @@ int check_ordinates(rom_handle* h, int n, const double* dirs, const double* w)
     return ROM_OK;
 }
 
+// defined with the choice of sweep kernels
+bool single_sweep_by_scan(const std::vector<SysInput>& in, rom_si_opts& o);
+
 }  // namespace
 
 // ====================================================================================== C ABI
@@ -1969,8 +1973,6 @@ int rom_create(const rom_grid* grid, const double* sigma_t, const double* sigma_
         h->dy = (grid->y1 - grid->y0) / grid->ny;
         h->cells = cells;
         h->st.assign(sigma_t, sigma_t + cells);
-        for (int64_t i = h->grid.nx; i < cells; i += h->grid.nx)
-            h->row_changes += std::memcmp(&h->st[i], &h->st[i - h->grid.nx], h->grid.nx * sizeof(double)) != 0;
         h->ss.assign(sigma_s, sigma_s + cells);
         h->q.assign(q, q + cells);
         for (int f = 0; f < 4; ++f)
@@ -2098,7 +2100,7 @@ int rom_sweep(rom_handle* h, const double* src, int32_t src_per_ordinate, double
             if (!isfin(src[k])) return fail(h, ROM_E_DOMAIN, "non-finite source");
         std::vector<SysInput> in{{h, h->dirs.data(), h->w.data(), h->n, true}};
         std::unique_ptr<Plan> P(new Plan());
-        if (o.sweep == ROM_SWEEP_AUTO) o.sweep = ROM_SWEEP_STRIP;
+        if (o.sweep == ROM_SWEEP_AUTO && (per || psi || !single_sweep_by_scan(in, o))) o.sweep = ROM_SWEEP_STRIP;
         build_plan(*P, in, o, per ? 2 : 0, 0, psi != nullptr);
         hipStream_t s = h->stream();
         const SystemDev& sd = P->sys[0];
@@ -2129,7 +2131,7 @@ int rom_sweep(rom_handle* h, const double* src, int32_t src_per_ordinate, double
             HIPCHK(P->d_psi.alloc(tot * P->esz));
         }
         HIPCHK(launch_reset_systems(P->d_sysctl.as<SysCtl>(), 1, P->d_ctl.as<Ctl>(), s));
-        if (P->kind == ROM_SWEEP_DIAG) {
+        if (P->kind != ROM_SWEEP_STRIP) {
             HIPCHK(P->launch_sweep_any(1, s));
         } else {
             SweepArgs sa = P->sweep_args(1, psi_mode);
@@ -2200,8 +2202,8 @@ int rom::sweep_in_scratch(rom_handle* h, void* scratch, size_t cap, uint64_t* ow
             rom_si_opts o;
             std::memset(&o, 0, sizeof(o));
             o.precision = precision;
-            o.sweep = ROM_SWEEP_STRIP;  // as rom_sweep
             std::vector<SysInput> in{{h, h->dirs.data(), h->w.data(), h->n, true}};
+            if (!single_sweep_by_scan(in, o)) o.sweep = ROM_SWEEP_STRIP;  // as rom_sweep
             std::unique_ptr<Plan> P(new Plan());
             std::unique_ptr<Arena> ar(new Arena{(char*)scratch, cap, 0, s});
             P->arena = ar.get();
@@ -2224,13 +2226,18 @@ int rom::sweep_in_scratch(rom_handle* h, void* scratch, size_t cap, uint64_t* ow
         }
         Plan& P = *h->na_plan;
         h->na_arena->s = s;
-        // counters that must start at zero, then a fresh control state (ticket 0, epoch 1)
-        HIPCHK(launch_fill(P.d_prog.p, (int64_t)P.prog_count * 2, false, 0.0, s));
-        HIPCHK(launch_fill(P.d_ctl.p, (int64_t)(sizeof(Ctl) / 4), false, 0.0, s));
-        HIPCHK(launch_reset_systems(P.d_sysctl.as<SysCtl>(), 1, P.d_ctl.as<Ctl>(), s));
-        SweepArgs sa = P.sweep_args(1, 0);
-        sa.src = src;
-        HIPCHK(launch_sweep(sa, P.grid, P.fp64, P.tx, P.ty, P.dd, false, 0, P.L, 1, s));
+        if (P.kind == kSweepScan) {
+            HIPCHK(launch_reset_copy(src, P.src_ptr(), h->cells, P.fp64, P.d_sysctl.as<SysCtl>(), P.d_ctl.as<Ctl>(), s));
+            HIPCHK(P.launch_sweep_any(1, s));
+        } else {
+            // counters that must start at zero, then a fresh control state (ticket 0, epoch 1)
+            HIPCHK(launch_fill(P.d_prog.p, (int64_t)P.prog_count * 2, false, 0.0, s));
+            HIPCHK(launch_fill(P.d_ctl.p, (int64_t)(sizeof(Ctl) / 4), false, 0.0, s));
+            HIPCHK(launch_reset_systems(P.d_sysctl.as<SysCtl>(), 1, P.d_ctl.as<Ctl>(), s));
+            SweepArgs sa = P.sweep_args(1, 0);
+            sa.src = src;
+            HIPCHK(launch_sweep(sa, P.grid, P.fp64, P.tx, P.ty, P.dd, false, 0, P.L, 1, s));
+        }
         CombineArgs ca = P.combine_args(1, 0.0);
         ca.phi = phi;
         ca.src = nullptr;
@@ -2309,6 +2316,18 @@ void apply_choice(const TuneChoice& c, rom_si_opts& o)
     }
 }
 
+// Rows of a problem whose sigma_t differs from the row below (fields never change: counted once).
+int row_changes(rom_handle* h)
+{
+    if (h->row_changes < 0) {
+        const int64_t nx = h->grid.nx;
+        h->row_changes = 0;
+        for (int64_t i = nx; i < h->cells; i += nx)
+            h->row_changes += std::memcmp(&h->st[i], &h->st[i - nx], nx * sizeof(double)) != 0;
+    }
+    return h->row_changes;
+}
+
 // The row-scan shapes a batch can take: the single-ordinate form with the fewest cells per lane that
 // hold the widest row, then on 16-lane groups (one wavefront per workgroup where that holds a
 // quadrant), then the form for full GPUs with 8 and 16 wavefronts per workgroup.
@@ -2356,7 +2375,7 @@ bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode,
         maxn = std::max(maxn, s.n);
         ords += s.n;
         rows += h->grid.ny;
-        changes += h->row_changes;
+        changes += row_changes(s.h);
         // wavefronts with work, and wavefronts held, of 16-wavefront workgroups
         const ScanShape sh = scan_class_shape(scan_class(h->grid.nx));
         const int per = 64 / sh.G * sh.K, w = ((s.n + 3) / 4 + per - 1) / per * sh.strips;
@@ -2397,6 +2416,24 @@ bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode,
     if (maxnx <= 64 && (ords >= (fp64 ? 1024 : 2048) || (!fp64 && maxn >= 256 && maxny <= 100))) return take(4, 16);
     if (maxnx <= 128 && maxnx > 64 && (fp64 ? ords >= 4096 || (ords >= 2048 && maxny <= 128) : ords > 1024)) return take(4, 16);
     return take(4, 64);
+}
+
+// Whether one sweep with a shared source takes the row-scan sweep (160 x 120, 96 ordinates: a call 133 us, 316 on the
+// strip kernel, whose sweep alone is 152): the rule of the solves, for plans of up to 16 MiB.  Within
+// that the strip kernel's plan, too, fits the region of rom_sweep_noalloc, so no call is accepted or
+// refused there for the kernel it takes; both entry points decide alike and agree bit for bit.
+bool single_sweep_by_scan(const std::vector<SysInput>& in, rom_si_opts& o)
+{
+    if (o.scheme != ROM_SCHEME_STEP || o.tile_x != 0 || o.tile_y != 0 || o.band != 0 || o.diag_rows != 0 || o.diag_k != 0) return false;
+    TuneChoice pick;
+    if (!scan_rule(in, o, 0, pick) || pick.band > kScanWaves) return false;
+    const rom_handle* h = in[0].h;
+    const int64_t n = in[0].n, rows = h->grid.ny + 2 * kScanAhead;
+    const int64_t inflow = (n + 64) * (rows + 1024);   // of the entry faces, at most
+    const int64_t values = (n / 4 + 6) * h->cells + inflow + 8 * (2 * kScanAhead * (int64_t)h->grid.nx + 64);
+    if (values * (o.precision == ROM_PREC_FP64 ? 8 : 4) > (int64_t)16 << 20) return false;
+    apply_choice(pick, o);
+    return true;
 }
 
 // Time sweep + combine steps of every candidate on the real buffers of this batch shape (zero

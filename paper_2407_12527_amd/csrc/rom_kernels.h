@@ -215,6 +215,8 @@ hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStrea
 hipError_t launch_sweep_prologue(Ctl* ctl, hipStream_t s);
 hipError_t launch_mark(Ctl* ctl, hipStream_t s);
 hipError_t launch_reset_systems(SysCtl* sc, int nsys, Ctl* ctl, hipStream_t s);
+// the same for one system, with a copy of a caller's source of n values
+hipError_t launch_reset_copy(const void* in, void* src, int64_t n, bool fp64, SysCtl* sc, Ctl* ctl, hipStream_t s);
 hipError_t launch_fill(void* p, int64_t n, bool fp64, double v, hipStream_t s);
 // S = q for every system of a plan (the first source of source iteration)
 hipError_t launch_init_source(const SystemDev* sys, const ProblemDev* probs, int nsys, int64_t max_cells, bool fp64,

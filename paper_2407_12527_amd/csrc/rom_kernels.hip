@@ -538,6 +538,19 @@ __global__ void reset_systems_kernel(SysCtl* sc, int nsys, Ctl* ctl)
     if (s == 0) reset_ctl(ctl, nsys);
 }
 
+// One system's reset and the copy of its source into a padded pool (one launch before a single row-scan
+// sweep, which reads past its rows' ends).
+template <typename T>
+__global__ void reset_copy_kernel(const T* in, T* src, int64_t n, SysCtl* sc, Ctl* ctl)
+{
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 == 0) {
+        reset_system(sc[0]);
+        reset_ctl(ctl, 1);
+    }
+    for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * blockDim.x) src[i] = in[i];
+}
+
 template <typename T>
 __global__ void fill_kernel(T* p, int64_t n, T v)
 {
@@ -1262,6 +1275,14 @@ hipError_t launch_init_state(const SystemDev* sys, const ProblemDev* probs, int 
     else
         hipLaunchKernelGGL(init_state_kernel<float>, grid, dim3(256), 0, s, sys, probs, nsys, (const float*)q,
                            (float*)src, (float*)phi, phi_total, sc, ctl);
+    return hipGetLastError();
+}
+
+hipError_t launch_reset_copy(const void* in, void* src, int64_t n, bool fp64, SysCtl* sc, Ctl* ctl, hipStream_t s)
+{
+    const int nb = (int)std::min<int64_t>((n + 255) / 256, 4096);
+    if (fp64) hipLaunchKernelGGL(reset_copy_kernel<double>, dim3(nb), dim3(256), 0, s, (const double*)in, (double*)src, n, sc, ctl);
+    else hipLaunchKernelGGL(reset_copy_kernel<float>, dim3(nb), dim3(256), 0, s, (const float*)in, (float*)src, n, sc, ctl);
     return hipGetLastError();
 }
 
