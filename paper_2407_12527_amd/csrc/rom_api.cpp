@@ -343,7 +343,8 @@ struct Plan {
     DevMem d_stasks;
     int64_t pad = kPoolPad;  // elements of padding on both sides of the sigma_t and source pools
 
-    DevMem d_probs, d_sys, d_ws, d_lanes, d_tickets, d_slot_off, d_slot_order, d_slot_off_ord, d_cblocks;
+    DevMem d_probs, d_sys, d_ws, d_lanes, d_tickets, d_slot_off, d_slot_order, d_slot_off_ord, d_cblocks, d_pblocks;
+    int npblocks = 0;  // combine blocks as descriptors (evenly spaced partial planes)
     DevMem d_st, d_ss, d_q, d_src, d_phi, d_part, d_edge, d_inflow, d_prog, d_ctl, d_sysctl, d_rhist;
     DevMem d_ang, d_psi, d_Pt, d_uflags;
     DevMem d_kmsys, d_kmord, d_kmuidx, d_kmdense, d_kminv;  // kernel-matrix build inputs
@@ -485,6 +486,7 @@ struct Plan {
         c.slot_off = d_slot_off.as<int64_t>();
         c.slot_off_ord = d_slot_off_ord.as<int64_t>();
         c.blocks = d_cblocks.as<int2>();
+        c.pblocks = npblocks > 0 ? d_pblocks.as<CombineBlockDev>() : nullptr;
         c.cells_per_block = cells_per_block;
         c.many_cpt = many_cpt;
         c.vec = vec;
@@ -1141,7 +1143,7 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
                     }
                     wv += t.nw;
                     P.slot_off.push_back(part_sum);
-                    part_sum += h->cells * P.nmom;
+                    part_sum += ang_plane(h->cells * P.nmom);
                     sys_slots[sy].push_back(P.nslots);
                     ++P.nslots;
                     P.stasks.push_back(t);
@@ -1292,7 +1294,10 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
         // large tiles also sum more slots where they fill the GPU twice over: a block's fixed cost
         // (its count-in and its system's maxima, one address each) then matters more than the split
         const bool large = tot / (4 * 256 * V) >= 2 * device_cus();
-        if (maxslots > 8 && P.nmom == 1 && aligned && !large && vec_combine_enabled()) {
+        // the row-scan sweep's planes start on such a boundary and may be read past their end, and this
+        // kernel updates cell by cell: any cell count
+        const bool planes = P.kind == kSweepScan && !aligned;
+        if (((maxslots > 8 && aligned) || planes) && P.nmom == 1 && !large && vec_combine_enabled()) {
             P.vec = maxslots > 64 ? 3 : 1;  // 8 waves per block above 64 slots
             P.cells_per_block = 64 * V;
         } else if (P.nmom == 1 && aligned && vec_combine_enabled()) {
@@ -1322,6 +1327,30 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
     for (size_t i = 0; i < P.slot_order.size(); ++i) P.slot_off_ord[i] = P.slot_off[P.slot_order[i]];
     put(P, P.d_slot_off_ord, P.slot_off_ord);
     put(P, P.d_cblocks, P.cblocks);
+    if (P.kind == kSweepScan && (P.vec == 1 || P.vec == 3)) {
+        std::vector<CombineBlockDev> pb;
+        bool even = true;
+        for (const int2& b : P.cblocks) {
+            const SystemDev& sd = P.sys[b.x];
+            const int64_t* so = P.slot_off_ord.data() + sd.slot_first;
+            const int64_t cells = P.handles[sd.prob]->cells, stride = sd.nslots > 1 ? so[1] - so[0] : 0;
+            for (int k = 0; k < sd.nslots && b.y == 0; ++k) even = even && so[k] == so[0] + k * stride;
+            CombineBlockDev d{};
+            d.part0 = (sd.nslots > 0 ? so[0] : 0) + b.y;
+            d.stride = stride;
+            d.phi_off = sd.phi_off + b.y;
+            d.src_off = sd.src_off + b.y;
+            d.field_off = P.probs[sd.prob].field_off + b.y;
+            d.cells = (int)std::min<int64_t>(P.cells_per_block, cells - b.y);
+            d.nslots = sd.nslots;
+            d.sys = b.x;
+            pb.push_back(d);
+        }
+        if (even) {
+            put(P, P.d_pblocks, pb);
+            P.npblocks = (int)pb.size();
+        }
+    }
     put(P, P.d_uflags, uflags);
     put(P, P.d_dtasks, P.dtasks);
     put(P, P.d_stasks, P.stasks);

@@ -78,6 +78,16 @@ struct ScanArgs {
     int32_t pad;
 };
 
+// A block of the combine step with everything it addresses (elements).
+struct CombineBlockDev {
+    int64_t part0, stride;     // its cells in the system's first partial plane; from one plane to the next
+    int64_t phi_off, src_off, field_off;  // its cells in those pools
+    int32_t cells;             // its cells
+    int32_t nslots;
+    int32_t sys;
+    int32_t pad;
+};
+
 struct CombineArgs {
     const SystemDev* sys;
     const ProblemDev* probs;
@@ -85,6 +95,7 @@ struct CombineArgs {
     const int64_t* slot_off;
     const int64_t* slot_off_ord;  // slot_off[slot_order[i]]: offsets in summation order
     const int2* blocks;        // (system, first cell) per block
+    const CombineBlockDev* pblocks;  // the same blocks for evenly spaced planes (vec 1 and 3), NULL: none
     int32_t cells_per_block;
     int32_t many_cpt;          // 0: one wave sums all slots of 4 cells per thread; 1, 2, 4, 8: the
                                // many-slot combine, tiles of 64 * many_cpt cells (= cells_per_block)

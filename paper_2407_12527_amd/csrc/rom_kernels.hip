@@ -102,11 +102,17 @@ __device__ __forceinline__ void combine_tail(const CombineArgs& A, bool run, int
     }
     __syncthreads();
     if (s_last) {
+        // the clock words are loaded ahead of the finalize step's own chain of loads
+        unsigned long long t_last = 0, t_first = 0, t_mark = 0;
+        if (tid == 0) {
+            t_last = __hip_atomic_load(&A.ctl->t_last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            t_first = A.ctl->t_first;
+            t_mark = A.ctl->t_mark;
+        }
         if (A.mode == 0) finalize_iteration(A);
         if (tid == 0) {
-            const unsigned long long t_last = __hip_atomic_load(&A.ctl->t_last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (t_last > A.ctl->t_first && A.ctl->t_first != ~0ull) {
-                const unsigned long long t0 = A.ctl->t_mark < A.ctl->t_first ? A.ctl->t_mark : A.ctl->t_first;
+            if (t_last > t_first && t_first != ~0ull) {
+                const unsigned long long t0 = t_mark < t_first ? t_mark : t_first;
                 A.ctl->sweep_ticks += t_last - t0;
                 A.ctl->sweeps += 1;
             }
@@ -303,7 +309,7 @@ __global__ __launch_bounds__(64 * NW) void combine_vec_kernel(CombineArgs A)
         const int ns = SD.nslots;
         const int64_t* __restrict__ soff = A.slot_off_ord + SD.slot_first;
         const int c0 = blk.y + lane * V;
-        const bool in = c0 < cells;  // cells is a multiple of V: a lane's V cells are all in or all out
+        const bool in = c0 < cells;  // the last lane's V cells may reach past the last one: padding of the plane
         V4 acc[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) acc[u] = V4{};
@@ -333,6 +339,78 @@ __global__ __launch_bounds__(64 * NW) void combine_vec_kernel(CombineArgs A)
         pmax = fabs((double)v);
         phi[ucell] = v;
         if (A.mode == 0) src[ucell] = fma(ssv, v, qv);
+    }
+    combine_tail(A, run, s, dmax, pmax);
+}
+
+// The same for evenly spaced planes (the row-scan sweep's): a block's addresses come from one descriptor
+// and arithmetic instead of the chain block, system, problem, slot list, each a trip to memory, which is
+// most of what a small combine waits for; the state of a lone system is that of the solve.  256^2, 256
+// planes: 35 us -> 26; FP64 96 x 80, 36 planes: 11.4 -> 8.7; 301 x 517, 100 planes: 38 (cell by cell,
+// combine_many_kernel) -> 25 by vectors -> 22.  What is left is the sweep's tail in other XCDs' caches
+// and three trips of the maxima, the count and the finalize step.
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void combine_planes_kernel(CombineArgs A)
+{
+    using V4 = typename Vec16<T>::type;
+    constexpr int V = 16 / sizeof(T);
+    constexpr int U = 16;
+    static_assert(NW == 4 || NW == 8, "4 or 8 waves");
+    typedef const __attribute__((address_space(4))) CombineBlockDev BlockDev;
+    const BlockDev& D = *((BlockDev*)A.pblocks + blockIdx.x);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int cells = D.cells, ns = D.nslots, s = D.sys;
+    if (A.mode == 0 && A.ctl->active == 0) return;
+    combine_clock(A);
+    const bool run = A.mode == 1 || A.nsys == 1 || A.sysctl[s].state == 0;
+    __shared__ T wsum[NW][64 * V];
+    double dmax = 0.0, pmax = 0.0;
+    const bool upd = run && tid < cells;
+    T* __restrict__ phi = (T*)A.phi + D.phi_off;
+    T old = T(0), ssv = T(0), qv = T(0);
+    if (upd) {
+        old = phi[tid];
+        if (A.mode == 0) {
+            ssv = ((const T*)A.sigma_s + D.field_off)[tid];
+            qv = ((const T*)A.q + D.field_off)[tid];
+        }
+    }
+    if (run) {
+        const int64_t stride = D.stride;
+        const T* p = (const T*)A.part + D.part0 + wave * stride + lane * V;
+        const bool in = lane * V < cells;  // the last lane's V cells may reach past the last one: padding of the plane
+        V4 acc[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = V4{};
+        int k = wave;
+        for (; k + NW * (U - 1) < ns; k += NW * U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (in) acc[u] += *(const V4*)p;
+                p += NW * stride;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (in && k + NW * u < ns) acc[u] += *(const V4*)p;
+            p += NW * stride;
+        }
+#pragma unroll
+        for (int h = U / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int u = 0; u < h; ++u) acc[u] += acc[u + h];
+        const T* tv = (const T*)&acc[0];
+#pragma unroll
+        for (int i = 0; i < V; ++i) wsum[wave][lane * V + i] = tv[i];
+    }
+    __syncthreads();
+    if (upd) {
+        T v = (wsum[0][tid] + wsum[1][tid]) + (wsum[2][tid] + wsum[3][tid]);
+        if constexpr (NW == 8) v += (wsum[4][tid] + wsum[5][tid]) + (wsum[6][tid] + wsum[7][tid]);
+        dmax = fabs((double)v - (double)old);
+        pmax = fabs((double)v);
+        phi[tid] = v;
+        if (A.mode == 0) ((T*)A.src + D.src_off)[tid] = fma(ssv, v, qv);
     }
     combine_tail(A, run, s, dmax, pmax);
 }
@@ -1166,7 +1244,15 @@ hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStrea
     if (a.vec == 1 || a.vec == 3) {
         // 4 waves per block; 8 for systems of more than 64 slots
         if (a.cells_per_block != 64 * (fp64 ? 2 : 4)) return hipErrorInvalidValue;
-        if (a.vec == 3) {
+        if (a.pblocks) {
+            if (a.vec == 3) {
+                if (fp64) hipLaunchKernelGGL((combine_planes_kernel<double, 8>), dim3(nblocks), dim3(512), 0, s, a);
+                else hipLaunchKernelGGL((combine_planes_kernel<float, 8>), dim3(nblocks), dim3(512), 0, s, a);
+            } else {
+                if (fp64) hipLaunchKernelGGL((combine_planes_kernel<double, 4>), dim3(nblocks), dim3(256), 0, s, a);
+                else hipLaunchKernelGGL((combine_planes_kernel<float, 4>), dim3(nblocks), dim3(256), 0, s, a);
+            }
+        } else if (a.vec == 3) {
             if (fp64) hipLaunchKernelGGL((combine_vec_kernel<double, 8>), dim3(nblocks), dim3(512), 0, s, a);
             else hipLaunchKernelGGL((combine_vec_kernel<float, 8>), dim3(nblocks), dim3(512), 0, s, a);
         } else {

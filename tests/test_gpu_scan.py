@@ -270,3 +270,30 @@ def test_single_sweeps(R, orc, nx, ny, n, prec):
         g.replay()
         torch.cuda.synchronize()
         assert np.array_equal(phi.double().cpu().numpy(), h.sweep(S, o))
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,n", [(1, 3, 1), (7, 11, 60), (61, 67, 66), (64, 33, 500), (31, 9, 2100)])
+def test_combine_of_planes(R, orc, nx, ny, n, prec):
+    """Cell counts that end inside a 16-byte load and inside a block of the combine, 4 to 64 planes and more (four
+    and eight wavefronts, more planes than are loaded at once), one system and three that stop apart."""
+    rng = np.random.default_rng([nx, ny, n])
+    st, ss, q = problem(rng, nx, ny, "uniform")
+    fp64 = prec == "fp64"
+    hs, refs, iters = [], [], []
+    for k in range(3):
+        h = R.Handle(nx, ny, st, ss * (0.2 + 0.4 * k), q)
+        d, w = R.generate_ordinates(R.ROM_ORD_IID_SPHERE, max(1, n - k), seed=k)
+        h.set_ordinates(d, w)
+        hs.append(h)
+        ref = orc.source_iterate(orc.Problem(nx, ny, st, ss * (0.2 + 0.4 * k), q), d, w, None, tol=1e-4, max_iter=50)
+        refs.append(ref["phi"])
+        iters.append(ref["iters"])
+    o = R.si_opts(tol=1e-4, max_iter=50, precision=R.ROM_PREC_FP64 if fp64 else R.ROM_PREC_FP32)
+    phi, s, _ = hs[1].source_iterate(o)
+    assert s.lanes == 1 and s.iters == iters[1]
+    parity.check(phi, refs[1], 1e-11 if fp64 else 1e-5)
+    phis, stats, _ = R.solve_batch(hs, o)
+    assert [x.iters for x in stats] == iters
+    for p, ref in zip(phis, refs):
+        parity.check(p, ref, 1e-11 if fp64 else 1e-5)
