@@ -1858,6 +1858,24 @@ SolveResult run_si(Plan& P, hipStream_t s, const rom_si_opts& o)
     return r;
 }
 
+// The scalar fluxes of systems 0 to count - 1 of one problem, [count][cells]: they lie one after the other,
+// so one copy (192 samples of 100^2 in FP64: 192 copies took 2.1 ms of a 4.6 ms call).
+void download_samples(const Plan& P, int count, double* out)
+{
+    const int64_t n = count * P.handles[0]->cells;
+    if (P.fp64) {
+        HIPCHK(hipMemcpy(out, P.d_phi.p, n * 8, hipMemcpyDeviceToHost));
+        return;
+    }
+    const int64_t part = std::min<int64_t>(n, (int64_t)1 << 22);   // 16 MiB of host memory at a time
+    std::unique_ptr<float[]> tmp(new float[part]);
+    for (int64_t k0 = 0; k0 < n; k0 += part) {
+        const int64_t m = std::min(part, n - k0);
+        HIPCHK(hipMemcpy(tmp.get(), P.d_phi.as<float>() + k0, m * 4, hipMemcpyDeviceToHost));
+        for (int64_t k = 0; k < m; ++k) out[k0 + k] = tmp[k];
+    }
+}
+
 void download_phi(const Plan& P, int sys, double* out)
 {
     const SystemDev& sd = P.sys[sys];
@@ -2865,7 +2883,7 @@ int rom_ensemble_samples(rom_handle* h, int32_t t, uint64_t seed, int64_t first,
     try {
         EnsAgg ag;
         auto download = [&](Plan& P, int done, int b) {
-            for (int k = 0; k < b; ++k) download_phi(P, k, phis + (size_t)(done + k) * h->cells);
+            download_samples(P, b, phis + (size_t)done * h->cells);
         };
         rc = ensemble_batches(h, first, t, seed, *spec, o, download, ag);
         if (rc) return rc;
