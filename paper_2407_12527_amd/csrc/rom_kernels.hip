@@ -535,9 +535,28 @@ __global__ __launch_bounds__(256) void combine_moments_kernel(CombineArgs A)
         const int c1 = min(cells, blk.y + A.cells_per_block);
         const T g = (T)SD.g;
         const int64_t pl = cells;
+        // The first slots' offsets are read once, and every load of a cell is issued before its sums: with
+        // the offsets' two loads ahead of each slot's (192 samples of 100^2, 4 slots, FP64) 88 us, so 60.
+        constexpr int F = 4;
+        const T* __restrict__ pf[F];
+#pragma unroll
+        for (int k = 0; k < F; ++k) pf[k] = k < ns ? part + soff[sord[k]] : nullptr;
         for (int cell = blk.y + tid; cell < c1; cell += 256) {
             T v0 = T(0), v1 = T(0), v2 = T(0), v3 = T(0);
-            for (int k = 0; k < ns; ++k) {
+            T a[F][4];
+#pragma unroll
+            for (int k = 0; k < F; ++k)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) a[k][m] = k < ns && (m < 3 || A.mom_r) ? pf[k][m * pl + cell] : T(0);
+            const T old = phi[cell], ssc = A.mode == 0 ? ss[cell] : T(0), qc = A.mode == 0 ? q[cell] : T(0);
+#pragma unroll
+            for (int k = 0; k < F; ++k) {
+                v0 += a[k][0];
+                v1 += a[k][1];
+                v2 += a[k][2];
+                v3 += a[k][3];
+            }
+            for (int k = F; k < ns; ++k) {
                 const T* __restrict__ pk = part + soff[sord[k]] + cell;
                 v0 += pk[0];
                 v1 += pk[pl];
@@ -545,13 +564,12 @@ __global__ __launch_bounds__(256) void combine_moments_kernel(CombineArgs A)
                 if (A.mom_r) v3 += pk[3 * pl];
             }
             if (!A.mom_r) v3 = v0;
-            const T old = phi[cell];
             dmax = fmax(dmax, fabs((double)v0 - (double)old));
             pmax = fmax(pmax, fabs((double)v0));
             phi[cell] = v0;
             if (A.mode == 0) {
-                const T sg = ss[cell] * g;
-                src[cell] = fma(ss[cell], v3, q[cell]);
+                const T sg = ssc * g;
+                src[cell] = fma(ssc, v3, qc);
                 src[pl + cell] = sg * v1;
                 src[2 * pl + cell] = sg * v2;
             }
