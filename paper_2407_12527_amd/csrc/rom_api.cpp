@@ -2404,23 +2404,29 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 //     128 rows (1000 x 64 x 36: 50 / 70; 1024^2 x 1024: 682 / 771, but 1024^2 x 256: 557 / 470);
 //   * 16-lane groups, four ordinates per wavefront, where one per wavefront would queue (64^2, 32
 //     samples of 64: 23 us against 27; 128^2 the same: 43 / 54; 64^2 x 80: 24 / 19);
+//   * batches of uneven grids below that give every grid the lanes of the widest: measured instead where
+//     their widths add up to more than 2800 (19 problems, mean width 330: 4.45 ms a solve against 4.04 on
+//     the row-lane kernel; 13 x 264: 3.75 / 3.21; but 11 x 226: 3.63 / 4.34; 10 x 179: 3.57 / 4.41);
 //   * the form for full GPUs from 2048 ordinates (256^2, 32 samples of 128: 130 us against 162;
 //     512^2: 319 / 775), from 4096 up to 128 columns and 16384 up to 64, where 16-lane groups carry
 //     further; with 16 wavefronts per workgroup where the partial planes it saves matter and its
-//     workgroups are full (512^2, 64 samples of 128: 467 us against 550; 24 uneven problems: 784 / 512).
+//     workgroups are full (512^2, 64 samples of 128: 467 us against 550; 24 uneven problems: 784 / 512)
+//     or run four times over (200 uneven problems, a solve: 37.6 ms against 38.5).
 bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode, TuneChoice& pick)
 {
     if (o.sweep != ROM_SWEEP_AUTO || (smode == 2 && o.scheme == ROM_SCHEME_DD)) return false;
     const bool fp64 = o.precision == ROM_PREC_FP64, dd = o.scheme == ROM_SCHEME_DD;
     const int mom = smode == 1 ? 4 : smode == 2 ? 0 : 1;
-    int maxnx = 0, maxny = 0, maxn = 0;
-    int64_t ords = 0, rows = 0, changes = 0, groups = 0, space = 0;
+    int maxnx = 0, minnx = 1 << 30, maxny = 0, maxn = 0;
+    int64_t ords = 0, widths = 0, rows = 0, changes = 0, groups = 0, space = 0;
     for (auto& s : in) {
         const rom_handle* h = s.h;
         maxnx = std::max(maxnx, h->grid.nx);
+        minnx = std::min(minnx, h->grid.nx);
         maxny = std::max(maxny, h->grid.ny);
         maxn = std::max(maxn, s.n);
         ords += s.n;
+        widths += h->grid.nx;
         rows += h->grid.ny;
         changes += row_changes(s.h);
         // wavefronts with work, and wavefronts held, of 16-wavefront workgroups
@@ -2456,12 +2462,13 @@ bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode,
     }
     if (maxnx > 64 && changes * 4 > rows) return false;
     if (maxnx > 512 && ords < 1024 && maxny > 128) return false;
-    const bool sixteen = space > 0 && groups * 10 >= space * 9;
+    const bool sixteen = space > 0 && (groups * 10 >= space * 9 || space / 16 * 4 >= 4 * device_cus());
     if (maxnx > 512) return fp64 ? take(4, 64) : take(ords >= 2048 && sixteen ? 16 : 8, 0);
     if (!fp64 && ords >= (maxnx <= 64 ? 16384 : maxnx <= 128 ? 4096 : 2048))
         return take(maxnx > 256 && ords >= 6144 && sixteen ? 16 : 8, 0);
+    if (2 * minnx <= maxnx && widths > 2800) return false;
     if (maxnx <= 64 && (ords >= (fp64 ? 1024 : 2048) || (!fp64 && maxn >= 256 && maxny <= 100))) return take(4, 16);
-    if (maxnx <= 128 && maxnx > 64 && (fp64 ? ords >= 4096 || (ords >= 2048 && maxny <= 128) : ords > 1024)) return take(4, 16);
+    if (maxnx <= 128 && maxnx > 64 && (fp64 ? ords >= 4096 || (ords >= 2048 && maxny <= 128) : ords >= 2048)) return take(4, 16);
     return take(4, 64);
 }
 

@@ -251,6 +251,27 @@ __device__ __forceinline__ float scan_rcp(float sg, float kap, float klo)
 }
 __device__ __forceinline__ double scan_rcp(double sg, double kap, double) { return rcp_fast(sg + kap); }
 
+// r and A = a r of a cell.  In a uniform medium every cell has the same coefficients, and with them the
+// same rounding errors, which add up along a row.  FP32 therefore rounds r and A with a dither that runs
+// evenly through +- half an ulp over the cells of a row (u1, u2), so that their mean over the row is
+// the exact value to a fraction of that.
+__device__ __forceinline__ float ulp_of(float x) { return __uint_as_float(__float_as_uint(x) & 0x7f800000u) * 0x1p-23f; }
+__device__ __forceinline__ void scan_coefficients(float sg, float kap, float klo, float a, float u1, float u2, float& r, float& A)
+{
+    const float d = sg + kap, v = d - sg;
+    const float lo = ((sg - (d - v)) + (kap - v)) + klo;
+    const float r0 = scan_rcp(sg, kap, klo);
+    const float rl = fma(-lo, r0, fma(-d, r0, 1.0f)) * r0;      // r0 + rl is 1 / (sg + a + b) to twice FP32
+    r = r0 + fma(u1, ulp_of(r0), rl);
+    const float ah = a * r0, al = fma(a, rl, fma(a, r0, -ah));
+    A = ah + fma(u2, ulp_of(ah), al);
+}
+__device__ __forceinline__ void scan_coefficients(double sg, double kap, double klo, double a, double, double, double& r, double& A)
+{
+    r = scan_rcp(sg, kap, klo);
+    A = a * r;
+}
+
 // ------------------------------------------------------------------------------------ row runs
 // N cells of a row in vector accesses of up to 16 bytes that need element alignment only: a uniform
 // base pointer and the lane's byte offset.  The N cells come in storage order.
@@ -379,8 +400,11 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
             T p = T(1);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                rr[k][c] = scan_rcp(sg[at(c)], kap, klo);
-                A[k][c] = a[k] * rr[k][c];
+                // a low-discrepancy dither by cell, another sequence for A
+                const int cell = (strip * G + pos) * C + c;
+                const T u1 = T((__brev((unsigned)cell) >> 8) * 0x1p-24f - 0.5f + 0x1p-12f);
+                const T u2 = T((((unsigned)cell * 0x9e3779b9u) >> 8) * 0x1p-24f - 0.5f);
+                scan_coefficients(sg[at(c)], kap, klo, a[k], u1, u2, rr[k][c], A[k][c]);
                 if constexpr (DD) X[k][c] = ((a[k] - b[k]) - sg[at(c)]) * rr[k][c];
                 p *= DD ? X[DD ? k : 0][DD ? c : 0] : A[k][c];
             }
