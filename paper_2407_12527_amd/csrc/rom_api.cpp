@@ -2452,6 +2452,17 @@ bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode,
             }
         return false;
     };
+    // What the other kernels take stays accepted: grids beyond the row scan's 32-bit byte offsets, and batches
+    // whose partial planes (one per four ordinates and moment; at least eight ordinates in the form for
+    // full GPUs) would be more than 32 GiB, are left to them.
+    const int64_t esz = fp64 ? 8 : 4;
+    int64_t planes = 0;
+    for (auto& s : in) {
+        const int64_t cells = s.h->cells, nx = s.h->grid.nx;
+        if ((cells * 4 + (4 * kScanAhead + 1) * nx) * esz >= (int64_t)1 << 32) return false;
+        planes += cells * (mom == 4 ? 4 : 1) * (s.n / (!fp64 && mom == 1 && ords >= 16384 ? 8 : 4) + 4);
+    }
+    if (planes * esz > (int64_t)32 << 30) return false;
     if (mom == 4 || dd) return maxnx <= 512 && take(4, maxnx <= 64 && ords >= 4096 ? 16 : 64);
     // dense kernels: 64-lane groups, whose source planes are read in long runs (256^2 x 1024, sweep,
     // contraction and combine: 291 us against 486 on the row-lane kernel; 8 samples of 64^2 x 64: 26 / 54;
