@@ -6,9 +6,9 @@ HBM: ordinate ingestion, source iteration to convergence (sweeps + partial-flux 
 residual, replayed from captured HIP graphs), FP64 ensemble moments where the workload has samples,
 and the results left in HBM.  The default workload is c5, the largest single-GPU configuration: 200
 independent problems (grid sides 64..1024, 16..512 ordinates, random 8 x 8 block maps of cross
-sections) solved together, one persistent sweep launch per iteration.  The sweep shape the headline
-is timed with is pinned per workload (the fastest in full-solve timings), so that the timed work does
-not depend on a timing-based choice made in the same process.
+sections) solved together, one sweep launch per iteration.  The sweep kernel and shape follow from a
+rule on the workload's sizes, so that the timed work does not depend on a timing-based choice made in
+the same process; --sweep and the shape flags time the other kernels.
 
 The JSON line carries, besides the contract fields:
   * roofline -- the dominant kernel (the sweep): its achieved rate from its own launch durations
@@ -57,21 +57,20 @@ HBM_PEAK_GBS = 8000.0
 BYTES_PER_ISO_UPDATE = 20.0 / 64.0
 BYTES_PER_ANG_UPDATE = 6.0
 
-# The sweep shape each workload's headline is timed with: the fastest in full-solve timings on
-# MI355X (c3's band of 7 strips lies between the autotuner's candidates 4 and 8).
-PINNED = {
-    "c1": {"sweep": "diag", "diag_rows": 64, "diag_k": 1, "band": 2, "tile": "0x0"},
-    "c2": {"sweep": "diag", "diag_rows": 64, "diag_k": 2, "band": 4, "tile": "0x0"},
-    "c3": {"sweep": "strip", "tile": "16x16", "band": 7, "diag_rows": 0, "diag_k": 0},
-    "c4": {"sweep": "diag", "diag_rows": 16, "diag_k": 4, "band": 4, "tile": "0x0"},
-    "c5": {"sweep": "strip", "tile": "16x16", "band": 4, "diag_rows": 0, "diag_k": 0},
-}
+# The sweep shape each workload's headline is timed with: left open.  librom then takes the row-scan
+# sweep by a rule on sizes and media, without a measurement, so the timed work is the same in every
+# process.  Step times on MI355X against the fastest shape of the other kernels: c1 0.235 / 0.457 ms,
+# c2 0.480 / 0.665, c3 3.88 / 7.13, c4 3.05 / 5.52, c5 38.2 / 55.5.
+PINNED = {w: {"sweep": "auto", "tile": "0x0", "band": 0, "diag_rows": 0, "diag_k": 0} for w in ("c1", "c2", "c3", "c4", "c5")}
 
 # HBM bytes per sweep launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs (scaled by a 256 MiB copy:
-# 1 FETCH_SIZE KiB = 2 KiB read, 1 WRITE_SIZE KiB = 1 KiB written), for the pinned kernel shape of
-# each workload.  Reported only while the kernel sources hash to what was profiled and the run
-# used that shape; otherwise `traffic` is null.
+# 1 FETCH_SIZE KiB = 2 KiB read, 1 WRITE_SIZE KiB = 1 KiB written), for the row-scan sweep of each
+# workload (SCAN_TRAFFIC) and for shapes of the other two kernels (MEASURED_TRAFFIC).  Reported only
+# while the kernel sources hash to what was profiled and the run used that shape; else `traffic` is null.
 KERNEL_SOURCES = {
+    "row-scan": ["rom_common.h", "rom_device.h", "rom_scan.h", "rom_scan_f32.hip", "rom_scan_f32_many.hip",
+                 "rom_scan_f64.hip", "rom_scan_ang_f32.hip", "rom_scan_ang_f64.hip", "rom_scan_lin_f32.hip",
+                 "rom_scan_lin_f64.hip"],
     "row-lane": ["rom_common.h", "rom_device.h", "rom_diag.h", "rom_diag_f32.hip", "rom_diag_f32_ang.hip",
                  "rom_diag_f64.hip"],
     "strip": ["rom_common.h", "rom_device.h", "rom_sweep.h", "rom_sweep_f32_16x16.hip", "rom_sweep_f32_16x8.hip",
@@ -83,6 +82,14 @@ MEASURED_TRAFFIC = {  # workload: [(kernel family, shape as in config, source ha
     "c3": [("strip", {"sweep_tile": "16x16", "band": 7}, "1ae15ac46a2bed53", 827140000)],
     "c4": [("row-lane", {"rows_per_block": 16, "ordinates_per_lane": 4, "waves_per_group": 4}, "0598a01edc4a0c77", 459540000)],
     "c5": [("strip", {"sweep_tile": "16x16", "band": 4}, "1ae15ac46a2bed53", 3162290000)],
+}
+
+SCAN_TRAFFIC = {
+    "c1": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "9a8730968022d677", 690000)],
+    "c2": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "9a8730968022d677", 19530000)],
+    "c3": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 2, "waves_per_group": 16}, "9a8730968022d677", 543060000)],
+    "c4": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "9a8730968022d677", 478570000)],
+    "c5": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 2, "waves_per_group": 16}, "9a8730968022d677", 2504680000)],
 }
 
 
@@ -98,7 +105,7 @@ def kernel_hash(family):
 def measured_traffic(workload, config):
     """HBM bytes per launch of the profiled kernel, if this run used a profiled shape and the
     kernel sources still hash to the profiled ones (else None)."""
-    for family, shape, digest, nbytes in MEASURED_TRAFFIC.get(workload, []):
+    for family, shape, digest, nbytes in MEASURED_TRAFFIC.get(workload, []) + SCAN_TRAFFIC.get(workload, []):
         if config.get("sweep_kernel") == family and all(config.get(k) == v for k, v in shape.items()):
             return nbytes if kernel_hash(family) == digest else None
     return None
@@ -152,6 +159,8 @@ def solve_opts(a, R, wl, precision=None):
 def sweep_shape(shape):
     """The sweep kernel and shape a solve ran with (as rom_si_stats reports them)."""
     tx, ty, band, lanes, kind = shape
+    if lanes == 1:
+        return {"sweep_kernel": "row-scan", "lanes_per_group": ty, "ordinates_per_group": tx, "waves_per_group": band}
     if kind == 2:
         return {"sweep_kernel": "row-lane", "rows_per_block": ty, "ordinates_per_lane": tx, "waves_per_group": band}
     return {"sweep_kernel": "strip", "sweep_tile": f"{tx}x{ty}", "band": band, "lanes_per_group": lanes}
@@ -403,7 +412,7 @@ def main():
     if tot_sweeps > 0:
         avg_s = tot_sweep_ms / tot_sweeps / 1e3
         upd_per_launch = tot_upd / tot_sweeps  # every running system sweeps once per launch
-        kernel = "diag_kernel" if shape[4] == 2 else "sweep_kernel"
+        kernel = "scan_kernel" if shape[3] == 1 else "diag_kernel" if shape[4] == 2 else "sweep_kernel"
         roof = roofline(kernel, wl.scattering, fp64, upd_per_launch, avg_s, measured_traffic(a.workload, config),
                         copy_gbs)
     out = {
