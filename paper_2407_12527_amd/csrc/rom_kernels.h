@@ -107,7 +107,7 @@ struct CombineArgs {
     int32_t max_iter;
     int32_t mom_r;             // linear kernel: phi~ comes from plane 3 (else phi~ = phi)
     int32_t vec;               // 16-byte loads (every system's cell count a multiple of 16 B /
-                               // sizeof(T)): 1 many slots, tiles of 64 * 16 B of cells split over
+                               // sizeof(T), or with 1 and 3 the row-scan sweep's planes): 1 many slots, tiles of 64 * 16 B of cells split over
                                // the block's 4 waves by slot (3: 8 waves, above 64 slots); 2 every
                                // slot by one thread, 4 tiles of 256 * 16 B
     int32_t clock;             // 1: the sweep before it took no end stamp (row-scan sweeps)
