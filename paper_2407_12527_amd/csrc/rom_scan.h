@@ -258,12 +258,13 @@ __device__ __forceinline__ double scan_rcp(double sg, double kap, double) { retu
 __device__ __forceinline__ float ulp_of(float x) { return __uint_as_float(__float_as_uint(x) & 0x7f800000u) * 0x1p-23f; }
 __device__ __forceinline__ void scan_coefficients(float sg, float kap, float klo, float a, float u1, float u2, float& r, float& A)
 {
+    sg = fminf(sg, 0x1.fffffep127f);   // a sigma_t beyond FP32 came as infinite, whose error terms are NaN
     const float d = sg + kap, v = d - sg;
     const float lo = ((sg - (d - v)) + (kap - v)) + klo;
     const float r0 = scan_rcp(sg, kap, klo);
     const float rl = fma(-lo, r0, fma(-d, r0, 1.0f)) * r0;      // r0 + rl is 1 / (sg + a + b) to twice FP32
-    r = r0 + fma(u1, ulp_of(r0), rl);
     const float ah = a * r0, al = fma(a, rl, fma(a, r0, -ah));
+    r = r0 + fma(u1, ulp_of(r0), rl);
     A = ah + fma(u2, ulp_of(ah), al);
 }
 __device__ __forceinline__ void scan_coefficients(double sg, double kap, double klo, double a, double, double, double& r, double& A)
@@ -405,7 +406,8 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
                 const T u1 = T((__brev((unsigned)cell) >> 8) * 0x1p-24f - 0.5f + 0x1p-12f);
                 const T u2 = T((((unsigned)cell * 0x9e3779b9u) >> 8) * 0x1p-24f - 0.5f);
                 scan_coefficients(sg[at(c)], kap, klo, a[k], u1, u2, rr[k][c], A[k][c]);
-                if constexpr (DD) X[k][c] = ((a[k] - b[k]) - sg[at(c)]) * rr[k][c];
+                // (r may round to zero in a black cell, whose multiplier is -1)
+                if constexpr (DD) X[k][c] = rr[k][c] > T(0) ? ((a[k] - b[k]) - sg[at(c)]) * rr[k][c] : T(-1);
                 p *= DD ? X[DD ? k : 0][DD ? c : 0] : A[k][c];
             }
             scan_multipliers<T, G>(p, lane, m[k]);

@@ -297,3 +297,31 @@ def test_combine_of_planes(R, orc, nx, ny, n, prec):
     assert [x.iters for x in stats] == iters
     for p, ref in zip(phis, refs):
         parity.check(p, ref, 1e-11 if fp64 else 1e-5)
+
+
+@pytest.mark.parametrize("kernel", ["iso", "linear", "hg"])
+@pytest.mark.parametrize("scheme", ["step", "dd"])
+@pytest.mark.parametrize("nx,n", [(40, 13), (64, 64), (130, 29), (300, 8)])
+def test_sigma_t_beyond_fp32(R, orc, monkeypatch, nx, n, scheme, kernel):
+    """A black cell whose sigma_t has no FP32 value lets nothing through; the others keep their flux."""
+    if kernel == "hg" and scheme == "dd":
+        pytest.skip("dense kernels run the step scheme here")
+    ny = 21
+    st = np.ones(nx * ny)
+    st[5 * nx + nx // 2] = 1e39
+    ss, q = np.full(nx * ny, 0.5), np.ones(nx * ny)
+    d, w = R.generate_ordinates(R.ROM_ORD_IID_SPHERE, n, seed=1)
+    W = None if kernel == "iso" else orc.build_W(d, w, orc.SCAT_LINEAR if kernel == "linear" else orc.SCAT_HG, 0.7, fold=1)
+    ref = orc.source_iterate(orc.Problem(nx, ny, st, ss, q), d, w, W, tol=-1, max_iter=4,
+                             scheme=orc.SCHEME_DD if scheme == "dd" else orc.SCHEME_STEP)["phi"]
+    o = R.si_opts(tol=-1, max_iter=4, scheme=R.ROM_SCHEME_DD if scheme == "dd" else R.ROM_SCHEME_STEP)
+    forms = 2 if nx <= (64 if kernel == "hg" else 128) else 1
+    for k in range(forms + (2 if kernel == "iso" and scheme == "step" else 0)):
+        monkeypatch.setenv("ROM_SWEEP_SCAN", str(k + 1))
+        h = R.Handle(nx, ny, st, ss, q)
+        h.set_ordinates(d, w)
+        if kernel != "iso":
+            h.set_scattering(R.ROM_SCAT_LINEAR if kernel == "linear" else R.ROM_SCAT_HG, 0.7)
+        phi, s, _ = h.source_iterate(o)
+        assert s.lanes == 1
+        parity.check(phi, ref, 2e-3 if kernel == "hg" else 1e-5)
