@@ -24,7 +24,7 @@
 // ordinate per group (RAW) psi itself is exchanged and weighted as it is summed, which also forms
 // every moment plane of the linear kernel from one exchange; with several, their weighted sum, over
 // the lane groups too by permlane swaps.  Source rows are loaded U rows ahead.  Lanes past the row's
-// end compute on clamped addresses; nothing flows back from them.
+// end compute on clamped addresses; nothing flows back from them or into another lane group.
 //
 // Dense kernels (MODE 2) keep a plane of cells per ordinate, so a wavefront's source rows are as
 // contiguous as an isotropic source's; the weighted angular flux leaves from the exchange, where all of a
@@ -56,7 +56,9 @@ __device__ __forceinline__ double dpp_move(double old, double v)
 }
 
 // Scan stage controls: row_shr 1, 2, 4, 8, row_bcast 15 (lane 15 of each 16 to the next 16),
-// row_bcast 31 (lane 31 to the upper 32).
+// row_bcast 31 (lane 31 to the upper 32).  The FP32 broadcasts write the rows that they are for only (masks
+// 0xa and 0xc): with G = 32, lane 31 may lie past its row's end, on another system's values, and its
+// broadcast reaches the other group, where a factor of zero does not hold back an infinity or a NaN.
 template <int S>
 constexpr int scan_ctrl() { return S == 0 ? 0x111 : S == 1 ? 0x112 : S == 2 ? 0x114 : S == 3 ? 0x118 : S == 4 ? 0x142 : 0x143; }
 
@@ -102,6 +104,7 @@ __device__ __forceinline__ T scan_shift(T v, T x0, int pos)
 template <int G, int K>
 __device__ __forceinline__ void scan_lanes(double (&b)[K], const double (&m)[K][scan_stages<G>()], double (&x)[K], int pos)
 {
+    static_assert(G != 32, "the broadcasts write every row of 16 lanes");
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         double v = b[k];
@@ -118,10 +121,10 @@ __device__ __forceinline__ void scan_lanes(double (&b)[K], const double (&m)[K][
 // FP32: each stage is one v_fmac_f32 with its moved operand (the compiler keeps a separate move).
 // A DPP read needs two wait states after the write of its register: the other ordinates' stages
 // and the s_nop give them.  The last instruction moves the result up one lane into x.
-#define ROM_DPP(CTRL) CTRL " row_mask:0xf bank_mask:0xf"
-#define ROM_FMAC(B, M, CTRL) "v_fmac_f32_dpp " B ", " B ", " M " " ROM_DPP(CTRL) " bound_ctrl:0\n\t"
-#define ROM_SHR1_16 "row_shr:1"
-#define ROM_SHR1_64 "wave_shr:1"
+#define ROM_ROWS(CTRL, ROWS) CTRL " row_mask:" ROWS " bank_mask:0xf"
+#define ROM_DPP(CTRL) ROM_ROWS(CTRL, "0xf")
+#define ROM_FMAC_ROWS(B, M, CTRL, ROWS) "v_fmac_f32_dpp " B ", " B ", " M " " ROM_ROWS(CTRL, ROWS) " bound_ctrl:0\n\t"
+#define ROM_FMAC(B, M, CTRL) ROM_FMAC_ROWS(B, M, CTRL, "0xf")
 template <int G, int K>
 __device__ __forceinline__ void scan_lanes(float (&b)[K], const float (&m)[K][scan_stages<G>()], float (&x)[K], int pos)
 {
@@ -130,8 +133,8 @@ __device__ __forceinline__ void scan_lanes(float (&b)[K], const float (&m)[K][sc
         // two ordinates at a time
 #pragma unroll
         for (int k = 0; k + 1 < K; k += 2) {
-#define ROM_STAGE2(S, CTRL)                                                                              \
-    asm("s_nop 1\n\t" ROM_FMAC("%0", "%2", CTRL) ROM_FMAC("%1", "%3", CTRL)                              \
+#define ROM_STAGE2(S, CTRL, ROWS)                                                                        \
+    asm("s_nop 1\n\t" ROM_FMAC_ROWS("%0", "%2", CTRL, ROWS) ROM_FMAC_ROWS("%1", "%3", CTRL, ROWS)        \
         : "+v"(b[k]), "+v"(b[k + 1]) : "v"(m[k][S]), "v"(m[k + 1][S]))
             asm("s_nop 1\n\t"
                 ROM_FMAC("%0", "%2", "row_shr:1") ROM_FMAC("%1", "%3", "row_shr:1") "s_nop 0\n\t"
@@ -141,8 +144,8 @@ __device__ __forceinline__ void scan_lanes(float (&b)[K], const float (&m)[K][sc
                 : "+v"(b[k]), "+v"(b[k + 1])
                 : "v"(m[k][0]), "v"(m[k + 1][0]), "v"(m[k][1]), "v"(m[k + 1][1]), "v"(m[k][2]), "v"(m[k + 1][2]),
                   "v"(m[k][3]), "v"(m[k + 1][3]));
-            if constexpr (NS >= 5) ROM_STAGE2(4, "row_bcast:15");
-            if constexpr (NS >= 6) ROM_STAGE2(5, "row_bcast:31");
+            if constexpr (NS >= 5) ROM_STAGE2(4, "row_bcast:15", "0xa");
+            if constexpr (NS >= 6) ROM_STAGE2(5, "row_bcast:31", "0xc");
 #undef ROM_STAGE2
             if constexpr (G == 16)
                 asm("s_nop 1\n\tv_mov_b32_dpp %0, %2 " ROM_DPP("row_shr:1") "\n\tv_mov_b32_dpp %1, %3 " ROM_DPP("row_shr:1")
@@ -154,15 +157,16 @@ __device__ __forceinline__ void scan_lanes(float (&b)[K], const float (&m)[K][sc
     }
     if constexpr (K % 2 == 1) {
         constexpr int k = K - 1;
-#define ROM_STAGE1(S, CTRL) asm("s_nop 1\n\t" ROM_FMAC("%0", "%1", CTRL) : "+v"(b[k]) : "v"(m[k][S]))
+#define ROM_STAGE1(S, CTRL, ROWS) \
+    asm("s_nop 1\n\t" ROM_FMAC_ROWS("%0", "%1", CTRL, ROWS) : "+v"(b[k]) : "v"(m[k][S]))
         asm("s_nop 1\n\t"
             ROM_FMAC("%0", "%1", "row_shr:1") "s_nop 1\n\t"
             ROM_FMAC("%0", "%2", "row_shr:2") "s_nop 1\n\t"
             ROM_FMAC("%0", "%3", "row_shr:4") "s_nop 1\n\t"
             ROM_FMAC("%0", "%4", "row_shr:8") "s_nop 1"
             : "+v"(b[k]) : "v"(m[k][0]), "v"(m[k][1]), "v"(m[k][2]), "v"(m[k][3]));
-        if constexpr (NS >= 5) ROM_STAGE1(4, "row_bcast:15");
-        if constexpr (NS >= 6) ROM_STAGE1(5, "row_bcast:31");
+        if constexpr (NS >= 5) ROM_STAGE1(4, "row_bcast:15", "0xa");
+        if constexpr (NS >= 6) ROM_STAGE1(5, "row_bcast:31", "0xc");
 #undef ROM_STAGE1
         if constexpr (G == 16)
             asm("s_nop 1\n\tv_mov_b32_dpp %0, %1 " ROM_DPP("row_shr:1") : "+v"(x[k]) : "v"(b[k]));
@@ -178,10 +182,10 @@ __device__ __forceinline__ void scan_lanes(float (&b)[K], const float (&m)[K][sc
         }
     }
 }
+#undef ROM_ROWS
 #undef ROM_DPP
+#undef ROM_FMAC_ROWS
 #undef ROM_FMAC
-#undef ROM_SHR1_16
-#undef ROM_SHR1_64
 
 // One stage of a transposing sum over lane halves D = 32 or 16: lanes without bit D get
 // x(l) + x(l ^ D), lanes with bit D get y(l ^ D) + y(l) (the lower lane's value always first).

@@ -325,3 +325,33 @@ def test_sigma_t_beyond_fp32(R, orc, monkeypatch, nx, n, scheme, kernel):
         phi, s, _ = h.source_iterate(o)
         assert s.lanes == 1
         parity.check(phi, ref, 2e-3 if kernel == "hg" else 1e-5)
+
+
+@pytest.mark.parametrize("k", [2, 3])
+@pytest.mark.parametrize("nx,n", [(130, 29), (248, 64), (200, 8)])
+def test_a_neighbour_without_fp32_values(R, orc, monkeypatch, nx, n, k):
+    """Two lane groups of 32 share a wavefront: beside a batch member whose source is infinite in FP32, one
+    whose rows end before the lanes do keeps its flux, bit for bit."""
+    import ctypes as C
+    monkeypatch.setenv("ROM_SWEEP_SCAN", str(k))
+    ny = 9
+    st = np.ones(nx * ny)
+    d, w = R.generate_ordinates(R.ROM_ORD_IID_SPHERE, n, seed=1)
+    got = []
+    for bad in (1.0, 1e39):
+        hs = []
+        for q in (1.0, bad):
+            h = R.Handle(nx, ny, st, 0.5 * st, q * st)
+            h.set_ordinates(d, w)
+            hs.append(h)
+        outs = [np.zeros(nx * ny) for _ in hs]
+        stats = (R.rom_si_stats * 2)()
+        o = R.si_opts(tol=1e-5, max_iter=30)
+        rc = R.lib().rom_solve_batch((C.c_void_p * 2)(*[h.h for h in hs]), 2, C.byref(o),
+                                     (C.c_void_p * 2)(*[x.ctypes.data for x in outs]), stats)
+        assert rc == R.ROM_OK or bad > 1.0
+        assert stats[0].lanes == 1 and stats[0].status == R.ROM_OK
+        got.append(outs[0])
+    assert np.array_equal(*got)
+    ref = orc.source_iterate(orc.Problem(nx, ny, st, 0.5 * st, st), d, w, None, tol=-1, max_iter=stats[0].iters)["phi"]
+    parity.check(got[1], ref, 1e-5)
