@@ -253,14 +253,19 @@ __device__ __forceinline__ float scan_rcp(float sg, float kap, float klo)
     const float r = rcp_fast(d);
     return fma(fma(-lo, r, fma(-d, r, 1.0f)), r, r);
 }
-__device__ __forceinline__ double scan_rcp(double sg, double kap, double) { return rcp_fast(sg + kap); }
 
-// r and A = a r of a cell.  In a uniform medium every cell has the same coefficients, and with them the
-// same rounding errors, which add up along a row.  FP32 therefore rounds r and A with a dither that runs
-// evenly through +- half an ulp over the cells of a row (u1, u2), so that their mean over the row is
-// the exact value to a fraction of that.
+// Multipliers of a cell: r, A = a r and, for diamond difference, X = 2 A - 1.  In a uniform medium every
+// cell has the same ones, and with them the same rounding errors, which add up along a flight path.  FP32
+// evens them out in both directions:
+//   * along a row, A and X are rounded with a dither that runs evenly through +- half an ulp over the
+//     cells (u), so that their mean over a row is the exact value to a fraction of that;
+//   * from row to row the flux goes by b r in one column, which a dither over columns would leave with
+//     one error for good (16 x 1000 cells: 1.2e-5 of phi).  r is rounded to nearest, and b takes one of
+//     two neighbouring values by rows, so that its mean makes up for r (3.5e-6; scan_even).
+// The steps' own roundings remain.  `rho` is the relative rounding error of r, 1 / (r d) - 1.
 __device__ __forceinline__ float ulp_of(float x) { return __uint_as_float(__float_as_uint(x) & 0x7f800000u) * 0x1p-23f; }
-__device__ __forceinline__ void scan_coefficients(float sg, float kap, float klo, float a, float u1, float u2, float& r, float& A)
+template <bool DD>
+__device__ __forceinline__ void scan_coefficients(float sg, float kap, float klo, float a, float, float u, float& r, float& A, float& X, float& rho)
 {
     sg = fminf(sg, 0x1.fffffep127f);   // a sigma_t beyond FP32 came as infinite, whose error terms are NaN
     const float d = sg + kap, v = d - sg;
@@ -268,13 +273,39 @@ __device__ __forceinline__ void scan_coefficients(float sg, float kap, float klo
     const float r0 = scan_rcp(sg, kap, klo);
     const float rl = fma(-lo, r0, fma(-d, r0, 1.0f)) * r0;      // r0 + rl is 1 / (sg + a + b) to twice FP32
     const float ah = a * r0, al = fma(a, rl, fma(a, r0, -ah));
-    r = r0 + fma(u1, ulp_of(r0), rl);
-    A = ah + fma(u2, ulp_of(ah), al);
+    r = r0 + rl;
+    rho = ((r0 - r) + rl) * d;
+    A = ah + fma(u, ulp_of(ah), al);
+    if constexpr (DD) {
+        const float ah2 = ah + ah, xh = ah2 - 1.0f, xl = ah2 - (xh + 1.0f);
+        X = xh + fma(u, ulp_of(xh), fma(2.0f, al, xl));
+    }
 }
-__device__ __forceinline__ void scan_coefficients(double sg, double kap, double klo, double a, double, double, double& r, double& A)
+template <bool DD>
+__device__ __forceinline__ void scan_coefficients(double sg, double kap, double, double a, double b, double, double& r, double& A, double& X, double& rho)
 {
-    r = scan_rcp(sg, kap, klo);
+    r = rcp_fast(sg + kap);
     A = a * r;
+    if constexpr (DD) X = r > 0.0 ? ((a - b) - sg) * r : -1.0;
+    rho = 0.0;
+}
+
+// The two values of an ordinate's b in a lane: `lo`, and the next one up in a fraction `part` / 2^32 of
+// the rows, with the mean b (1 + rho).  The lowest bit of `part` keeps which of the two b itself is.
+struct ScanB {
+    uint32_t lo, part;
+    __device__ __forceinline__ float own() const { return __uint_as_float(lo + (part & 1)); }
+    __device__ __forceinline__ float at(uint32_t phase) const { return __uint_as_float(lo + (phase < part ? 1u : 0u)); }
+};
+__device__ __forceinline__ ScanB scan_even(float b, float rho)
+{
+    const uint32_t bits = __float_as_uint(b);
+    // rho in ulps of b, whose significand is a whole number of them; |rho| is at most half an ulp of r
+    float up = rho * (float)((bits & 0x7fffffu) | 0x800000u);
+    up = b > 0.0f ? fminf(fmaxf(up, -0x1.fffffep-1f), 0x1.fffffep-1f) : 0.0f;
+    const bool below = up < 0.0f;
+    if (below) up = fminf(up + 1.0f, 0x1.fffffep-1f);
+    return ScanB{bits - (below ? 1u : 0u), ((uint32_t)(up * 0x1p32f) & ~1u) | (below ? 1u : 0u)};
 }
 
 // ------------------------------------------------------------------------------------ row runs
@@ -308,6 +339,8 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* scalar_ptr
 {
     return (const __attribute__((address_space(4))) T*)p;
 }
+
+constexpr int kScanEven = 4;   // rows that share a value of b
 
 // Everything one task needs (uniform values).
 template <typename T>
@@ -382,6 +415,8 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
     constexpr auto at = [](int c) { return DIR > 0 ? c : C - 1 - c; };
 
     T a[K], b[K], w[K], lc[KM], ls[KM];
+    ScanB even[sizeof(T) == 4 ? K : 1];   // FP32: b[k] is the current rows' value
+    uint32_t phase = 0;
     T y[K][C], rr[K][C], A[K][C], m[K][NS];
     T X[DD ? K : 1][DD ? C : 1];   // diamond difference: the x-face multiplier 2 A - 1, without its cancellation
 #pragma unroll
@@ -389,6 +424,7 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
         const LaneDev& o = ords[g * K + k];
         a[k] = to_T<T>(DD ? 2.0 * o.a : o.a);
         b[k] = to_T<T>(DD ? 2.0 * o.b : o.b);
+        if constexpr (sizeof(T) == 4) even[k] = scan_even(b[k], 0.0f);
         w[k] = to_T<T>(o.w);
         if constexpr (MODE == 1) {
             lc[k] = to_T<T>(o.c);
@@ -399,20 +435,28 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
     }
     // multipliers of a row from its sigma_t
     auto coefficients = [&](const T (&sg)[C]) {
+        const bool whole = (strip * G + pos + 1) * C <= nx;   // no cell past the row's end
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const T kap = a[k] + b[k], kv = kap - a[k], klo = (a[k] - (kap - kv)) + (b[k] - kv);
-            T p = T(1);
+            T bk = b[k];
+            if constexpr (sizeof(T) == 4) bk = even[k].own();
+            const T kap = a[k] + bk, kv = kap - a[k], klo = (a[k] - (kap - kv)) + (bk - kv);
+            T p = T(1), err = T(0), err0 = T(0);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                // a low-discrepancy dither by cell, another sequence for A
+                // a low-discrepancy dither by cell
                 const int cell = (strip * G + pos) * C + c;
-                const T u1 = T((__brev((unsigned)cell) >> 8) * 0x1p-24f - 0.5f + 0x1p-12f);
-                const T u2 = T((((unsigned)cell * 0x9e3779b9u) >> 8) * 0x1p-24f - 0.5f);
-                scan_coefficients(sg[at(c)], kap, klo, a[k], u1, u2, rr[k][c], A[k][c]);
-                // (r may round to zero in a black cell, whose multiplier is -1)
-                if constexpr (DD) X[k][c] = rr[k][c] > T(0) ? ((a[k] - b[k]) - sg[at(c)]) * rr[k][c] : T(-1);
-                p *= DD ? X[DD ? k : 0][DD ? c : 0] : A[k][c];
+                const T u = T((((unsigned)cell * 0x9e3779b9u) >> 8) * 0x1p-24f - 0.5f);
+                T rho, Xc;
+                scan_coefficients<DD>(sg[at(c)], kap, klo, a[k], bk, u, rr[k][c], A[k][c], Xc, rho);
+                if constexpr (DD) X[k][c] = Xc;
+                p *= DD ? Xc : A[k][c];
+                if (c == 0) err0 = rho;
+                err += rho;
+            }
+            if constexpr (sizeof(T) == 4) {
+                even[k] = scan_even(bk, whole ? err * (1.0f / C) : err0);   // the lane's cells in the mean
+                b[k] = even[k].at(phase);
             }
             scan_multipliers<T, G>(p, lane, m[k]);
         }
@@ -641,6 +685,14 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
                 }
                 // rows past the last one (a ragged last batch) compute on padding and are not summed
                 const int jj = js + u;
+                if constexpr (sizeof(T) == 4) {
+                    // (in a golden-ratio sequence every run of rows has its share)
+                    if (u % kScanEven == 0 && (U >= kScanEven || bi % (kScanEven / U) == 0)) {
+                        phase += 0x9e3779b9u;
+#pragma unroll
+                        for (int k = 0; k < K; ++k) b[k] = even[k].at(phase);
+                    }
+                }
                 if (__builtin_expect(jj == nc, 0)) {
                     if constexpr (AHEAD) {
                         coefficients(sg);

@@ -355,3 +355,46 @@ def test_a_neighbour_without_fp32_values(R, orc, monkeypatch, nx, n, k):
     assert np.array_equal(*got)
     ref = orc.source_iterate(orc.Problem(nx, ny, st, 0.5 * st, st), d, w, None, tol=-1, max_iter=stats[0].iters)["phi"]
     parity.check(got[1], ref, 1e-5)
+
+
+@pytest.mark.parametrize("scheme", ["step", "dd"])
+@pytest.mark.parametrize("nx,ny", [(16, 1000), (64, 1024), (130, 1000), (500, 700)])
+def test_long_columns_of_one_medium(R, orc, monkeypatch, nx, ny, scheme):
+    """One ordinate along the columns: the flux decays by the same b r in every row, whose rounding error must not
+    add up (1e-5 after 1000 rows is 1e-8 a row, a sixth of half an ulp, kept up all the way; the two roundings of
+    a row are as good as random while the flux decays, 1.1e-6 after 1000 rows, 5.6e-6 at five sigma).  The bar of
+    the other FP32 comparisons, here for every cell as well; twice that for diamond difference, whose face
+    values 2 psi - psi_in double a row's rounding."""
+    st, z = np.full(nx * ny, 0.1), np.zeros(nx * ny)
+    infl = {f: np.ones(ny if f in FACES[:2] else nx) for f in FACES}
+    dd = scheme == "dd"
+    p = orc.Problem(nx, ny, st, z, z, inflow=infl)
+    o = R.si_opts(tol=-1, max_iter=1, scheme=R.ROM_SCHEME_DD if dd else R.ROM_SCHEME_STEP)
+    for s in (0.777, -0.777, 0.9, -0.9):
+        d, w = np.array([[0.0, s, np.sqrt(1.0 - s * s)]]), np.ones(1)
+        ref = orc.scalar_flux(w, orc.sweep(p, d, z, scheme=orc.SCHEME_DD if dd else orc.SCHEME_STEP))
+        for k in range((2 if nx <= 128 else 1) + (0 if dd else 2)):
+            monkeypatch.setenv("ROM_SWEEP_SCAN", str(k + 1))
+            h = R.Handle(nx, ny, st, z, z, inflow=infl)
+            h.set_ordinates(d, w)
+            phi, stats, _ = h.source_iterate(o)
+            assert stats.lanes == 1
+            bar = 2e-5 if dd else 1e-5
+            parity.check(phi, ref, bar, cell_tol=bar, what=f"{s} form {k + 1}")
+
+
+@pytest.mark.parametrize("nx,ny", [(16, 1000), (64, 1024), (130, 600), (300, 700)])
+def test_tall_grids(R, orc, monkeypatch, nx, ny):
+    """The forms on grids far taller than a batch of rows, at the bars of the other FP32 solves."""
+    st = np.full(nx * ny, 1.0)
+    ss, q = 0.5 * st, np.zeros(nx * ny)
+    q.reshape(ny, nx)[ny // 3:ny // 2, nx // 4:] = 1.0
+    d, w = R.generate_ordinates(R.ROM_ORD_STRATIFIED, 2, 4, seed=2)
+    ref = orc.source_iterate(orc.Problem(nx, ny, st, ss, q), d, w, None, tol=-1, max_iter=5)["phi"]
+    for k in range(shapes(False, nx)):
+        monkeypatch.setenv("ROM_SWEEP_SCAN", str(k + 1))
+        h = R.Handle(nx, ny, st, ss, q)
+        h.set_ordinates(d, w)
+        phi, stats, _ = h.source_iterate(R.si_opts(tol=-1, max_iter=5))
+        assert stats.lanes == 1
+        parity.check(phi, ref, 1e-5)
