@@ -1308,8 +1308,11 @@ void build_plan(Plan& P, const std::vector<SysInput>& in, const rom_si_opts& o, 
             while (P.many_cpt < 8 && tot / (64 * 2 * P.many_cpt) > 4 * device_cus()) P.many_cpt *= 2;
             P.cells_per_block = 64 * P.many_cpt;
         } else {
-            int64_t cpb = (tot / 512 + 1023) / 1024 * 1024;
-            P.cells_per_block = (int)std::max<int64_t>(1024, std::min<int64_t>(cpb, 16384));
+            // a thread sums all slots of its cells, one cell after the other: one cell each where the slots are
+            // many and the GPU is not full
+            const int64_t least = maxslots > 4 && P.nmom == 4 ? 256 : 1024;
+            int64_t cpb = (tot / 512 + least - 1) / least * least;
+            P.cells_per_block = (int)std::max<int64_t>(least, std::min<int64_t>(cpb, 16384));
         }
     }
     for (int s = 0; s < P.nsys; ++s)
@@ -2375,6 +2378,19 @@ int row_changes(rom_handle* h)
     return h->row_changes;
 }
 
+// What the rule below looks at in a system.
+struct RuleSystem {
+    int nx, ny, n;
+    int64_t changes;   // rows whose sigma_t differs from the row below
+};
+
+std::vector<RuleSystem> rule_systems(const std::vector<SysInput>& in)
+{
+    std::vector<RuleSystem> r;
+    for (auto& s : in) r.push_back({s.h->grid.nx, s.h->grid.ny, s.n, row_changes(s.h)});
+    return r;
+}
+
 // The row-scan shapes a batch can take: the single-ordinate form with the fewest cells per lane that
 // hold the widest row, then on 16-lane groups (one wavefront per workgroup where that holds a
 // quadrant), then the form for full GPUs with 8 and 16 wavefronts per workgroup.
@@ -2407,12 +2423,17 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 //   * batches of uneven grids below that give every grid the lanes of the widest: measured instead where
 //     their widths add up to more than 2800 (19 problems, mean width 330: 4.45 ms a solve against 4.04 on
 //     the row-lane kernel; 13 x 264: 3.75 / 3.21; but 11 x 226: 3.63 / 4.34; 10 x 179: 3.57 / 4.41);
+//   * the linear kernel up to the ordinates where the combine's sum over their moment planes, one plane
+//     per four ordinates (16 on 16-lane groups), takes longer than the strip kernel's way through the grid
+//     (FP32: 16 us + 0.036 per ordinate + 0.2 per row against 8 + 0.65 per row and column, FP64 18 + 0.044 + 0.3
+//     against 10 + 2.4, in steps of 8^2 to 300 x 40 cells with 256 to 4096 ordinates; 32^2 x 512: 35 / 40,
+//     32^2 x 1024: 54 / 41, 64^2 x 1024: 63 / 94);
 //   * the form for full GPUs from 2048 ordinates (256^2, 32 samples of 128: 130 us against 162;
 //     512^2: 319 / 775), from 4096 up to 128 columns and 16384 up to 64, where 16-lane groups carry
 //     further; with 16 wavefronts per workgroup where the partial planes it saves matter and its
 //     workgroups are full (512^2, 64 samples of 128: 467 us against 550; 24 uneven problems: 784 / 512)
 //     or run four times over (200 uneven problems, a solve: 37.6 ms against 38.5).
-bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode, TuneChoice& pick)
+bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smode, TuneChoice& pick)
 {
     if (o.sweep != ROM_SWEEP_AUTO || (smode == 2 && o.scheme == ROM_SCHEME_DD)) return false;
     const bool fp64 = o.precision == ROM_PREC_FP64, dd = o.scheme == ROM_SCHEME_DD;
@@ -2420,17 +2441,16 @@ bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode,
     int maxnx = 0, minnx = 1 << 30, maxny = 0, maxn = 0;
     int64_t ords = 0, widths = 0, rows = 0, changes = 0, groups = 0, space = 0;
     for (auto& s : in) {
-        const rom_handle* h = s.h;
-        maxnx = std::max(maxnx, h->grid.nx);
-        minnx = std::min(minnx, h->grid.nx);
-        maxny = std::max(maxny, h->grid.ny);
+        maxnx = std::max(maxnx, s.nx);
+        minnx = std::min(minnx, s.nx);
+        maxny = std::max(maxny, s.ny);
         maxn = std::max(maxn, s.n);
         ords += s.n;
-        widths += h->grid.nx;
-        rows += h->grid.ny;
-        changes += row_changes(s.h);
+        widths += s.nx;
+        rows += s.ny;
+        changes += s.changes;
         // wavefronts with work, and wavefronts held, of 16-wavefront workgroups
-        const ScanShape sh = scan_class_shape(scan_class(h->grid.nx));
+        const ScanShape sh = scan_class_shape(scan_class(s.nx));
         const int per = 64 / sh.G * sh.K, w = ((s.n + 3) / 4 + per - 1) / per * sh.strips;
         groups += w;
         space += (w + 15) / 16 * 16;
@@ -2458,12 +2478,19 @@ bool scan_rule(const std::vector<SysInput>& in, const rom_si_opts& o, int smode,
     const int64_t esz = fp64 ? 8 : 4;
     int64_t planes = 0;
     for (auto& s : in) {
-        const int64_t cells = s.h->cells, nx = s.h->grid.nx;
+        const int64_t nx = s.nx, cells = nx * s.ny;
         if ((cells * 4 + (4 * kScanAhead + 1) * nx) * esz >= (int64_t)1 << 32) return false;
         planes += cells * (mom == 4 ? 4 : 1) * (s.n / (!fp64 && mom == 1 && ords >= 16384 ? 8 : 4) + 4);
     }
     if (planes * esz > (int64_t)32 << 30) return false;
-    if (mom == 4 || dd) return maxnx <= 512 && take(4, maxnx <= 64 && ords >= 4096 ? 16 : 64);
+    if (mom == 4 || dd) {
+        const bool sixteen = maxnx <= 64 && ords >= 4096;
+        if (mom == 4) {
+            const int64_t most = fp64 ? 55 * maxnx + 48 * maxny - 180 : 18 * maxnx + 25 * maxny / 2 - 220;
+            if (maxn > (sixteen ? 4 : 1) * most) return false;
+        }
+        return maxnx <= 512 && take(4, sixteen ? 16 : 64);
+    }
     // dense kernels: 64-lane groups, whose source planes are read in long runs (256^2 x 1024, sweep,
     // contraction and combine: 291 us against 486 on the row-lane kernel; 8 samples of 64^2 x 64: 26 / 54;
     // FP64 96 x 80: 51 / 331 on the strip kernel)
@@ -2491,7 +2518,7 @@ bool single_sweep_by_scan(const std::vector<SysInput>& in, rom_si_opts& o)
 {
     if (o.scheme != ROM_SCHEME_STEP || o.tile_x != 0 || o.tile_y != 0 || o.band != 0 || o.diag_rows != 0 || o.diag_k != 0) return false;
     TuneChoice pick;
-    if (!scan_rule(in, o, 0, pick) || pick.band > kScanWaves) return false;
+    if (!scan_rule(rule_systems(in), o, 0, pick) || pick.band > kScanWaves) return false;
     const rom_handle* h = in[0].h;
     const int64_t n = in[0].n, rows = h->grid.ny + 2 * kScanAhead;
     const int64_t inflow = (n + 64) * (rows + 1024);   // of the entry faces, at most
@@ -2605,7 +2632,7 @@ int solve_systems(rom_handle* owner, std::vector<SysInput>& in, const rom_si_opt
                                                           : (o.tile_x == 0 && o.band == 0);
         TuneChoice scan;
         if (free_shape && autotune_enabled()) {
-            if (scan_rule(in, o, smode, scan)) apply_choice(scan, o);
+            if (scan_rule(rule_systems(in), o, smode, scan)) apply_choice(scan, o);
             else autotune(owner, in, o, smode, owner->stream());
         }
         slot.reset(new Plan());
@@ -2715,6 +2742,26 @@ int ensemble_batches(rom_handle* h, int64_t first, int t, uint64_t seed, const r
 }  // namespace
 
 extern "C" {
+
+// The rule's choice for `count` systems of {nx, ny, ordinates, row changes} in shape[0..2]: wavefronts, lanes
+// per row and cells per lane (zero in the form for full GPUs); returns 0 where it leaves them to the
+// other kernels.  Host arithmetic, not part of the interface: the tests ask it about sizes that no test can run.
+int rom_scan_rule(const int64_t* systems, int32_t count, int32_t precision, int32_t scheme, int32_t smode, int32_t* shape)
+{
+    std::vector<RuleSystem> in;
+    for (int k = 0; k < count; ++k)
+        in.push_back({(int)systems[4 * k], (int)systems[4 * k + 1], (int)systems[4 * k + 2], systems[4 * k + 3]});
+    rom_si_opts o;
+    std::memset(&o, 0, sizeof(o));
+    o.precision = precision;
+    o.scheme = scheme;
+    TuneChoice c;
+    if (!scan_rule(in, o, smode, c)) return 0;
+    shape[0] = c.band;
+    shape[1] = c.rows;
+    shape[2] = c.tx;
+    return 1;
+}
 
 int rom_source_iterate(rom_handle* h, const rom_si_opts* opts, double* phi, rom_si_stats* stats)
 {

@@ -1,0 +1,65 @@
+"""The rule that takes the row-scan sweep, asked about sizes on the host: the limits of its kernels and its lines."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+ISO, LINEAR, DENSE = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def R():
+    from paper_2407_12527_amd import rom
+    rom.lib()
+    return rom
+
+
+def choice(R, systems, prec="fp32", mode=ISO, dd=False):
+    """(wavefronts, lanes per row, cells per lane), or None where the other kernels are left the choice.
+    systems: (nx, ny, ordinates[, rows whose sigma_t differs from the row below])."""
+    f = R.lib().rom_scan_rule
+    a = np.array([s if len(s) == 4 else (*s, 0) for s in systems], dtype=np.int64)
+    out = (C.c_int32 * 3)()
+    got = f(C.c_void_p(a.ctypes.data), len(a), R.ROM_PREC_FP64 if prec == "fp64" else R.ROM_PREC_FP32,
+            R.ROM_SCHEME_DD if dd else R.ROM_SCHEME_STEP, mode, out)
+    return tuple(out) if got else None
+
+
+def test_offsets_within_a_system_are_32_bit(R):
+    # (cells * 4 planes + 33 rows of look-ahead) * bytes per value below 4 GiB
+    for prec, esz in (("fp32", 4), ("fp64", 8)):
+        most = (2**32 // esz - 1 - 33 * 512) // (4 * 512)   # rows of 512 cells
+        assert choice(R, [(512, most, 4)], prec) is not None
+        assert choice(R, [(512, most + 1, 4)], prec) is None
+
+
+def test_partial_planes_fit_32_gib(R):
+    # a plane per four ordinates and quadrant remainder: 64 + 4 of 512 x 512 cells in FP64 a system
+    most = 2**35 // (512 * 512 * 68 * 8)
+    assert choice(R, [(512, 512, 256)] * most, "fp64") is not None
+    assert choice(R, [(512, 512, 256)] * (most + 1), "fp64") is None
+    # four times that with the linear kernel's moments
+    most = 2**35 // (512 * 512 * 68 * 8 * 4)
+    assert choice(R, [(512, 512, 256)] * most, "fp64", LINEAR) is not None
+    assert choice(R, [(512, 512, 256)] * (most + 1), "fp64", LINEAR) is None
+
+
+def test_widths(R):
+    assert choice(R, [(512, 64, 16)], mode=DENSE) == (4, 64, 8)
+    for mode, dd in ((LINEAR, False), (LINEAR, True), (ISO, True), (DENSE, False)):
+        assert choice(R, [(512, 200, 16)], mode=mode, dd=dd) is not None
+        assert choice(R, [(513, 200, 16)], mode=mode, dd=dd) is None
+    assert choice(R, [(64, 64, 16)], mode=DENSE, dd=True) is None
+    assert choice(R, [(1024, 100, 16)]) is not None
+    assert choice(R, [(1025, 100, 16)]) is None
+
+
+# One system of the linear kernel: the row scan where it is the faster one (step times in the rule's comment).
+@pytest.mark.parametrize("prec,nx,ny,n,taken", [
+    ("fp32", 8, 8, 256, False), ("fp32", 16, 16, 512, False), ("fp32", 16, 16, 4096, False), ("fp32", 32, 32, 512, True),
+    ("fp32", 32, 32, 1024, False), ("fp32", 32, 32, 4096, False), ("fp32", 64, 64, 1024, True), ("fp32", 64, 64, 2048, False),
+    ("fp32", 64, 64, 4096, True), ("fp32", 100, 100, 2048, True), ("fp64", 8, 8, 256, True), ("fp64", 8, 8, 1024, False),
+    ("fp64", 8, 8, 4096, False), ("fp64", 16, 16, 512, True), ("fp64", 16, 16, 2048, False), ("fp64", 32, 32, 2048, True)])
+def test_linear_kernel_with_many_ordinates(R, prec, nx, ny, n, taken):
+    assert (choice(R, [(nx, ny, n)], prec, LINEAR) is not None) == taken
+    assert choice(R, [(nx, ny, n)], prec, ISO, dd=True) is not None
