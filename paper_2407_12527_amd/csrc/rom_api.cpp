@@ -2428,6 +2428,13 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 //     (FP32: 16 us + 0.036 per ordinate + 0.2 per row against 8 + 0.65 per row and column, FP64 18 + 0.044 + 0.3
 //     against 10 + 2.4, in steps of 8^2 to 300 x 40 cells with 256 to 4096 ordinates; 32^2 x 512: 35 / 40,
 //     32^2 x 1024: 54 / 41, 64^2 x 1024: 63 / 94);
+//   * the linear kernel and diamond difference in FP32 until the GPU is full, where the strip kernel, whose lanes
+//     are ordinates, updates more cells at once: by W updates a step, the row scan takes 1 us per 0.55 million
+//     (0.47 beyond 256 columns, 0.85 on 16-lane groups) with the linear kernel and 1.45 million, times the part
+//     of its lanes that the row fills, with diamond difference; the strip kernel 0.53 us per row and column and
+//     1 us per 1.35 million, and 0.45 and 4.2 million, times the part of its lanes that have ordinates (linear, 256^2:
+//     16 samples of 128 227 / 379, 64 of them 948 / 617; 300^2, 512 ordinates: 16 samples 1483 / 721; diamond
+//     difference, 256^2: 16 samples of 512 437 / 317, 32 of 128 206 / 305; FP64 never within 16384 ordinates);
 //   * the form for full GPUs from 2048 ordinates (256^2, 32 samples of 128: 130 us against 162;
 //     512^2: 319 / 775), from 4096 up to 128 columns and 16384 up to 64, where 16-lane groups carry
 //     further; with 16 wavefronts per workgroup where the partial planes it saves matter and its
@@ -2440,7 +2447,9 @@ bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smod
     const int mom = smode == 1 ? 4 : smode == 2 ? 0 : 1;
     int maxnx = 0, minnx = 1 << 30, maxny = 0, maxn = 0;
     int64_t ords = 0, widths = 0, rows = 0, changes = 0, groups = 0, space = 0;
+    double updates = 0.0;   // of a step
     for (auto& s : in) {
+        updates += (double)s.nx * s.ny * s.n;
         maxnx = std::max(maxnx, s.nx);
         minnx = std::min(minnx, s.nx);
         maxny = std::max(maxny, s.ny);
@@ -2488,6 +2497,15 @@ bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smod
         if (mom == 4) {
             const int64_t most = fp64 ? 55 * maxnx + 48 * maxny - 180 : 18 * maxnx + 25 * maxny / 2 - 220;
             if (maxn > (sixteen ? 4 : 1) * most) return false;
+        }
+        if (!fp64 && maxnx <= 512) {
+            const int nq = (maxn + 3) / 4, L = nq <= 16 ? 16 : nq <= 32 ? 32 : 64;
+            const double fill = maxn / (4.0 * L * ((nq + L - 1) / L)), side = maxnx + maxny;
+            int C = (maxnx + 63) / 64;
+            while (!scan_supported(fp64, 4, 64, C, mom, dd)) ++C;
+            const double scan = mom == 4 ? updates / (sixteen ? 0.85 : maxnx > 256 ? 0.47 : 0.55) : updates / (1.45 * maxnx / (sixteen ? 64.0 : 64.0 * C));
+            const double strip = mom == 4 ? 0.53e6 * side + updates / (1.35 * fill) : 0.45e6 * side + updates / (4.2 * fill);
+            if (scan > strip) return false;
         }
         return maxnx <= 512 && take(4, sixteen ? 16 : 64);
     }

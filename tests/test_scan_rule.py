@@ -63,3 +63,16 @@ def test_widths(R):
 def test_linear_kernel_with_many_ordinates(R, prec, nx, ny, n, taken):
     assert (choice(R, [(nx, ny, n)], prec, LINEAR) is not None) == taken
     assert choice(R, [(nx, ny, n)], prec, ISO, dd=True) is not None
+
+
+# Ensembles that fill the GPU in FP32, diamond difference and the linear kernel: the strip kernel where it is the faster one.
+@pytest.mark.parametrize("mode,dd,nx,n,t,taken", [
+    (LINEAR, False, 256, 128, 16, True), (LINEAR, False, 256, 128, 64, False), (LINEAR, False, 128, 128, 32, True),
+    (LINEAR, False, 128, 128, 64, False), (LINEAR, False, 300, 128, 16, True), (LINEAR, False, 300, 128, 32, False),
+    (LINEAR, True, 512, 128, 8, True), (LINEAR, True, 512, 128, 16, False), (LINEAR, False, 64, 128, 128, True),
+    (LINEAR, False, 128, 32, 256, True), (ISO, True, 256, 128, 32, True), (ISO, True, 256, 128, 64, False),
+    (ISO, True, 300, 128, 16, True), (ISO, True, 300, 128, 32, False), (ISO, True, 300, 32, 128, True),
+    (ISO, True, 512, 128, 16, True), (ISO, True, 512, 512, 8, False), (ISO, True, 64, 128, 128, True)])
+def test_ensembles_that_fill_the_gpu(R, mode, dd, nx, n, t, taken):
+    assert (choice(R, [(nx, nx, n)] * t, "fp32", mode, dd) is not None) == taken
+    assert choice(R, [(nx, nx, n)] * t, "fp64", mode, dd) is not None
