@@ -2439,7 +2439,10 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 //     512^2: 319 / 775), from 4096 up to 128 columns and 16384 up to 64, where 16-lane groups carry
 //     further; with 16 wavefronts per workgroup where the partial planes it saves matter and its
 //     workgroups are full (512^2, 64 samples of 128: 467 us against 550; 24 uneven problems: 784 / 512)
-//     or run four times over (200 uneven problems, a solve: 37.6 ms against 38.5).
+//     or run four times over (200 uneven problems, a solve: 37.6 ms against 38.5);
+//   * not that form for hundreds of small samples of 64 ordinates or fewer, whose quadrants leave most of a
+//     workgroup's eight wavefronts idle: up to 64 columns any (64^2, 256 samples of 64: 77 us against 67; 512 of
+//     32: 156 / 89), up to 128 columns more than 300 (128^2, 512 samples of 32: 303 / 261; 256 of them 145 / 177).
 bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smode, TuneChoice& pick)
 {
     if (o.sweep != ROM_SWEEP_AUTO || (smode == 2 && o.scheme == ROM_SCHEME_DD)) return false;
@@ -2520,6 +2523,7 @@ bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smod
     if (maxnx > 512 && ords < 1024 && maxny > 128) return false;
     const bool sixteen = space > 0 && (groups * 10 >= space * 9 || space / 16 * 4 >= 4 * device_cus());
     if (maxnx > 512) return fp64 ? take(4, 64) : take(ords >= 2048 && sixteen ? 16 : 8, 0);
+    if (!fp64 && maxn <= 64 && ((maxnx <= 64 && ords >= 12288) || (maxnx <= 128 && in.size() > 300 && ords >= 4096))) return false;
     if (!fp64 && ords >= (maxnx <= 64 ? 16384 : maxnx <= 128 ? 4096 : 2048))
         return take(maxnx > 256 && ords >= 6144 && sixteen ? 16 : 8, 0);
     if (2 * minnx <= maxnx && widths > 2800) return false;

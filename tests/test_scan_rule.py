@@ -76,3 +76,12 @@ def test_linear_kernel_with_many_ordinates(R, prec, nx, ny, n, taken):
 def test_ensembles_that_fill_the_gpu(R, mode, dd, nx, n, t, taken):
     assert (choice(R, [(nx, nx, n)] * t, "fp32", mode, dd) is not None) == taken
     assert choice(R, [(nx, nx, n)] * t, "fp64", mode, dd) is not None
+
+
+# Hundreds of small samples with few ordinates: the measured choice (step times in the rule's comment).
+@pytest.mark.parametrize("nx,n,t,taken", [
+    (32, 16, 1024, False), (64, 64, 256, False), (64, 32, 512, False), (64, 32, 256, True), (64, 128, 128, True), (100, 8, 512, False),
+    (100, 32, 256, True), (128, 48, 341, False), (128, 32, 256, True), (128, 128, 512, True), (200, 16, 512, True)])
+def test_many_small_samples(R, nx, n, t, taken):
+    assert (choice(R, [(nx, nx, n)] * t) is not None) == taken
+    assert choice(R, [(nx, nx, n)] * t, "fp64") is not None
