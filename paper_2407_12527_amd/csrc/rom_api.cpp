@@ -2412,8 +2412,12 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 // shape: a rule, not a measurement, so a problem always sums in the same order.  The lines come from
 // step times (sweep and combine) of 240 shapes, 32^2 to 1024^2 cells and 8 to 8192 ordinates in all:
 //   * media whose sigma_t changes in more than a quarter of the rows rebuild the multipliers too
-//     often: beyond 64 columns the row-lane kernel is faster (256^2, 100 ordinates, random sigma_t:
-//     74 us against 87; 64 columns: 26.1 against 25.1);
+//     often, and the row-lane kernel is faster (random sigma_t: 256^2, 100 ordinates 74 us against 87, 64^2 25
+//     against 33, 24 x 200 41 against 80).  FP32 up to 128 columns, where a row has less to gain: more than a
+//     fifth (every fourth row, 32 x 60, 16 ordinates 19 against 22, 100 ordinates 24 / 22), but not for 32
+//     such rows or fewer a problem, where it is 3 us at most (40 x 28, 48 ordinates 17.5 / 20.5; 60 x 20
+//     18.9 / 17.6).  FP64 up to 64 columns, where a rebuild is short: 0.3 us per row and 8 in all against 0.25
+//     per row and column and 5 (64^2 33 / 27, 32^2 23 / 18, but 24 x 200 59 / 62, 8 x 64 22 / 27);
 //   * up to 512 columns it beat the row-lane kernel on every other shape (64^2 x 256: 22 us against
 //     30; 256^2 x 256: 62 / 84; 512^2 x 256: 142 / 197; FP64 256^2 x 256: 79 / 158) and the strip
 //     kernel by 1.6 to 12 times; beyond, where there are 1024 ordinates to fill the GPU or at most
@@ -2519,7 +2523,10 @@ bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smod
         pick = c[0];
         return maxnx <= 512 && changes * 4 <= rows;
     }
-    if (maxnx > 64 && changes * 4 > rows) return false;
+    if (fp64 && maxnx <= 64 ? changes * 4 > rows && 5 * maxnx <= maxny + 60
+        : fp64 || maxnx > 128 ? changes * 4 > rows
+                              : changes * 5 > rows && changes > 32 * (int64_t)in.size())
+        return false;
     if (maxnx > 512 && ords < 1024 && maxny > 128) return false;
     const bool sixteen = space > 0 && (groups * 10 >= space * 9 || space / 16 * 4 >= 4 * device_cus());
     if (maxnx > 512) return fp64 ? take(4, 64) : take(ords >= 2048 && sixteen ? 16 : 8, 0);

@@ -85,3 +85,16 @@ def test_ensembles_that_fill_the_gpu(R, mode, dd, nx, n, t, taken):
 def test_many_small_samples(R, nx, n, t, taken):
     assert (choice(R, [(nx, nx, n)] * t) is not None) == taken
     assert choice(R, [(nx, nx, n)] * t, "fp64") is not None
+
+
+# Media that change from row to row: the row-lane kernel where it is the faster one (step times in the rule's comment).
+@pytest.mark.parametrize("prec,nx,ny,changes,taken", [
+    ("fp32", 8, 64, 63, False), ("fp32", 24, 200, 199, False), ("fp32", 64, 64, 63, False), ("fp32", 64, 300, 299, False),
+    ("fp32", 28, 40, 39, False), ("fp32", 60, 20, 19, True), ("fp32", 32, 200, 40, True), ("fp32", 32, 200, 41, False),
+    ("fp32", 300, 100, 25, True), ("fp32", 300, 100, 26, False), ("fp64", 64, 64, 63, True), ("fp64", 32, 32, 31, True),
+    ("fp64", 8, 64, 63, False), ("fp64", 24, 200, 199, False), ("fp64", 65, 64, 63, False), ("fp64", 65, 64, 16, True)])
+def test_media_that_change_from_row_to_row(R, prec, nx, ny, changes, taken):
+    assert (choice(R, [(nx, ny, 64, changes)], prec) is not None) == taken
+    assert (choice(R, [(nx, ny, 64, changes)] * 3, prec) is not None) == taken
+    assert choice(R, [(nx, ny, 64, 0)], prec) is not None
+    assert choice(R, [(nx, ny, 64, changes)], prec, dd=True) is not None   # the strip kernel is slower there in any medium
