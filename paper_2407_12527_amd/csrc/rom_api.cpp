@@ -2661,7 +2661,8 @@ int solve_systems(rom_handle* owner, std::vector<SysInput>& in, const rom_si_opt
                                                           : (o.tile_x == 0 && o.band == 0);
         TuneChoice scan;
         if (free_shape && autotune_enabled()) {
-            if (scan_rule(rule_systems(in), o, smode, scan)) apply_choice(scan, o);
+            // a caller who names rows or ordinates per lane asks for those among the other kernels' shapes
+            if (o.diag_rows == 0 && o.diag_k == 0 && scan_rule(rule_systems(in), o, smode, scan)) apply_choice(scan, o);
             else autotune(owner, in, o, smode, owner->stream());
         }
         slot.reset(new Plan());

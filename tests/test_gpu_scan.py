@@ -398,3 +398,18 @@ def test_tall_grids(R, orc, monkeypatch, nx, ny):
         phi, stats, _ = h.source_iterate(R.si_opts(tol=-1, max_iter=5))
         assert stats.lanes == 1
         parity.check(phi, ref, 1e-5)
+
+
+@pytest.mark.parametrize("shape", [{"diag_rows": 16}, {"diag_rows": 64}, {"diag_k": 2}, {"diag_rows": 16, "diag_k": 1}])
+def test_a_named_row_lane_shape_is_kept(R, orc, shape):
+    """Rows or ordinates per lane, named with the kernel left open, restrict the choice as before: among the row-lane
+    kernel's shapes those, or the strip kernel's, never the row scan."""
+    f = problem(np.random.default_rng(1), 48, 40, "uniform")
+    d, w = R.generate_ordinates(R.ROM_ORD_IID_SPHERE, 24, seed=1)
+    h = R.Handle(48, 40, *f)
+    h.set_ordinates(d, w)
+    phi, s, _ = h.source_iterate(R.si_opts(tol=-1, max_iter=4, **shape))
+    assert s.lanes != 1
+    if s.sweep == R.ROM_SWEEP_DIAG:
+        assert s.tile_y == shape.get("diag_rows", s.tile_y) and s.tile_x == shape.get("diag_k", s.tile_x)
+    parity.check(phi, orc.source_iterate(orc.Problem(48, 40, *f), d, w, None, tol=-1, max_iter=4)["phi"], 1e-5)
