@@ -210,6 +210,7 @@ struct rom_handle {
     int64_t cells = 0;
     std::vector<double> st, ss, q;
     int row_changes = -1;       // rows whose sigma_t differs from the row below (-1: not counted yet)
+    double top = 0.0;           // largest value of q and of the faces' inflow
     std::vector<double> face[4];
     // ordinates in the caller's order
     int n = 0;
@@ -1999,6 +2000,7 @@ int rom_create(const rom_grid* grid, const double* sigma_t, const double* sigma_
         !(grid->y1 > grid->y0))
         return fail(nullptr, ROM_E_ARG, "grid box must satisfy x1 > x0, y1 > y0");
     const int64_t cells = (int64_t)grid->nx * grid->ny;
+    double top = 0.0;
     for (int64_t k = 0; k < cells; ++k) {
         const double st = sigma_t[k], ss = sigma_s[k], qq = q[k];
         if (!isfin(st) || !isfin(ss) || !isfin(qq)) return fail(nullptr, ROM_E_DOMAIN, "non-finite field value");
@@ -2006,14 +2008,17 @@ int rom_create(const rom_grid* grid, const double* sigma_t, const double* sigma_
         if (ss < 0.0) return fail(nullptr, ROM_E_DOMAIN, "sigma_s must be >= 0");
         if (!(ss < st)) return fail(nullptr, ROM_E_DOMAIN, "sigma_s must be < sigma_t");
         if (qq < 0.0) return fail(nullptr, ROM_E_DOMAIN, "q must be >= 0");
+        top = std::max(top, qq);
     }
     const double* faces[4] = {inflow ? inflow->left : nullptr, inflow ? inflow->right : nullptr,
                               inflow ? inflow->bottom : nullptr, inflow ? inflow->top : nullptr};
     for (int f = 0; f < 4; ++f) {
         if (!faces[f]) continue;
         const int len = f < 2 ? grid->ny : grid->nx;
-        for (int k = 0; k < len; ++k)
+        for (int k = 0; k < len; ++k) {
             if (!isfin(faces[f][k]) || faces[f][k] < 0.0) return fail(nullptr, ROM_E_DOMAIN, "inflow must be finite and >= 0");
+            top = std::max(top, faces[f][k]);
+        }
     }
     std::unique_ptr<rom_handle> h(new (std::nothrow) rom_handle());
     if (!h) return fail(nullptr, ROM_E_NOMEM, "host allocation failed");
@@ -2022,6 +2027,7 @@ int rom_create(const rom_grid* grid, const double* sigma_t, const double* sigma_
         h->dx = (grid->x1 - grid->x0) / grid->nx;
         h->dy = (grid->y1 - grid->y0) / grid->ny;
         h->cells = cells;
+        h->top = top;
         h->st.assign(sigma_t, sigma_t + cells);
         h->ss.assign(sigma_s, sigma_s + cells);
         h->q.assign(q, q + cells);
@@ -2382,12 +2388,18 @@ int row_changes(rom_handle* h)
 struct RuleSystem {
     int nx, ny, n;
     int64_t changes;   // rows whose sigma_t differs from the row below
+    double top = 0.0;  // largest source or inflow
 };
 
 std::vector<RuleSystem> rule_systems(const std::vector<SysInput>& in)
 {
     std::vector<RuleSystem> r;
-    for (auto& s : in) r.push_back({s.h->grid.nx, s.h->grid.ny, s.n, row_changes(s.h)});
+    for (auto& s : in) {
+        double top = s.h->top;
+        for (int f = 0; f < 4 && s.use_angular; ++f)
+            for (const double v : s.h->ang[f]) top = std::max(top, v);
+        r.push_back({s.h->grid.nx, s.h->grid.ny, s.n, row_changes(s.h), top});
+    }
     return r;
 }
 
@@ -2500,6 +2512,10 @@ bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smod
     }
     if (planes * esz > (int64_t)32 << 30) return false;
     if (mom == 4 || dd) {
+        // the strip kernel carries fluxes times their weights and so reaches further towards the end of FP32:
+        // sources within a factor of 1e8 of it are left to it
+        for (auto& s : in)
+            if (!fp64 && s.top > 1e30 && s.top <= 3.402823466e38) return false;
         const bool sixteen = maxnx <= 64 && ords >= 4096;
         if (mom == 4) {
             const int64_t most = fp64 ? 55 * maxnx + 48 * maxny - 180 : 18 * maxnx + 25 * maxny / 2 - 220;
@@ -2780,7 +2796,7 @@ int rom_scan_rule(const int64_t* systems, int32_t count, int32_t precision, int3
 {
     std::vector<RuleSystem> in;
     for (int k = 0; k < count; ++k)
-        in.push_back({(int)systems[4 * k], (int)systems[4 * k + 1], (int)systems[4 * k + 2], systems[4 * k + 3]});
+        in.push_back({(int)systems[4 * k], (int)systems[4 * k + 1], (int)systems[4 * k + 2], systems[4 * k + 3], 0.0});
     rom_si_opts o;
     std::memset(&o, 0, sizeof(o));
     o.precision = precision;

@@ -413,3 +413,27 @@ def test_a_named_row_lane_shape_is_kept(R, orc, shape):
     if s.sweep == R.ROM_SWEEP_DIAG:
         assert s.tile_y == shape.get("diag_rows", s.tile_y) and s.tile_x == shape.get("diag_k", s.tile_x)
     parity.check(phi, orc.source_iterate(orc.Problem(48, 40, *f), d, w, None, tol=-1, max_iter=4)["phi"], 1e-5)
+
+
+@pytest.mark.parametrize("kernel,dd,top", [("iso", True, 1e37), ("linear", True, 1e37), ("linear", False, 2e37)])
+@pytest.mark.parametrize("where", ["q", "inflow", "angular"])
+def test_sources_near_the_end_of_fp32(R, orc, kernel, dd, top, where):
+    """The weighted fluxes of the strip kernel stay finite where 2 |s| / dy times the flux itself would not."""
+    nx, ny, n = 40, 24, 29
+    one, z = np.ones(nx * ny), np.zeros(nx * ny)
+    d, w = R.generate_ordinates(R.ROM_ORD_IID_SPHERE, n, seed=1)
+    q = top * one if where == "q" else z
+    infl = {"left": np.full(ny, top)} if where == "inflow" else None
+    W = None if kernel == "iso" else orc.build_W(d, w, orc.SCAT_LINEAR, 0.8, fold=1)
+    h = R.Handle(nx, ny, one, 0.5 * one, q, inflow=infl)
+    h.set_ordinates(d, w)
+    ang = None
+    if where == "angular":
+        h.set_inflow_angular(0, np.full((n, ny), top))
+        ang = {"left": np.full((n, ny), top)}
+    if kernel != "iso":
+        h.set_scattering(R.ROM_SCAT_LINEAR, 0.8)
+    phi, s, _ = h.source_iterate(R.si_opts(tol=-1, max_iter=6, scheme=R.ROM_SCHEME_DD if dd else R.ROM_SCHEME_STEP))
+    ref = orc.source_iterate(orc.Problem(nx, ny, one, 0.5 * one, q, inflow=infl, inflow_angular=ang), d, w, W, tol=-1, max_iter=6,
+                             scheme=orc.SCHEME_DD if dd else orc.SCHEME_STEP)["phi"]
+    parity.check(phi, ref, 1e-5)
