@@ -60,15 +60,19 @@ __device__ void finalize_iteration(const CombineArgs& A)
 }
 
 // A row-scan sweep takes no stamp at its end (its workgroups claim no tickets): it ends where the
-// combine step starts.  Device scope, since another XCD's block reads it in combine_tail.
+// combine step starts (CLOCK).  Device scope, since another XCD's block reads it in combine_tail.  The combines
+// of the other sweeps are compiled without it: asked for at run time it took 0.5 us of their steps (16 x 16
+// cells, row-lane 12.8 us -> 12.2).
+template <bool CLOCK>
 __device__ __forceinline__ void combine_clock(const CombineArgs& A)
 {
-    if (A.clock && blockIdx.x == 0 && threadIdx.x == 0)
+    if (CLOCK && blockIdx.x == 0 && threadIdx.x == 0)
         __hip_atomic_store(&A.ctl->t_last, wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Block maxima (wave reduction, then across the 4 waves), the per-system FP64 maxima as atomics,
 // and the last block's finalize of the iteration.
+template <bool CLOCK>
 __device__ __forceinline__ void combine_tail(const CombineArgs& A, bool run, int s, double dmax, double pmax)
 {
     const int tid = threadIdx.x;
@@ -104,13 +108,18 @@ __device__ __forceinline__ void combine_tail(const CombineArgs& A, bool run, int
     if (s_last) {
         // the clock words are loaded ahead of the finalize step's own chain of loads
         unsigned long long t_last = 0, t_first = 0, t_mark = 0;
-        if (tid == 0) {
+        if (CLOCK && tid == 0) {
             t_last = __hip_atomic_load(&A.ctl->t_last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             t_first = A.ctl->t_first;
             t_mark = A.ctl->t_mark;
         }
         if (A.mode == 0) finalize_iteration(A);
         if (tid == 0) {
+            if constexpr (!CLOCK) {
+                t_last = A.ctl->t_last;
+                t_first = A.ctl->t_first;
+                t_mark = A.ctl->t_mark;
+            }
             if (t_last > t_first && t_first != ~0ull) {
                 const unsigned long long t0 = t_mark < t_first ? t_mark : t_first;
                 A.ctl->sweep_ticks += t_last - t0;
@@ -126,14 +135,14 @@ __device__ __forceinline__ void combine_tail(const CombineArgs& A, bool run, int
     }
 }
 
-template <typename T>
+template <typename T, bool CLOCK>
 __global__ __launch_bounds__(256) void combine_kernel(CombineArgs A)
 {
     const int tid = threadIdx.x;
     // Every block of a launch reads `active` before the last block of the same launch can change
     // it, so either all blocks of this launch return here or none does.
     if (A.mode == 0 && A.ctl->active == 0) return;
-    combine_clock(A);
+    combine_clock<CLOCK>(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -181,19 +190,19 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs A)
             }
         }
     }
-    combine_tail(A, run, s, dmax, pmax);
+    combine_tail<CLOCK>(A, run, s, dmax, pmax);
 }
 
 // Combine for systems with many partial slots (the row-lane sweep writes one per task): a block
 // owns 64 * CPT cells, its four waves sum interleaved quarters of the slot list (two independent
 // chains each, so loads stay in flight), and the per-cell total is formed in a fixed order,
 // ((w0 + w1) + (w2 + w3)), so results are deterministic.
-template <typename T, int CPT>
+template <typename T, int CPT, bool CLOCK>
 __global__ __launch_bounds__(256) void combine_many_kernel(CombineArgs A)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (A.mode == 0 && A.ctl->active == 0) return;
-    combine_clock(A);
+    combine_clock<CLOCK>(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -250,7 +259,7 @@ __global__ __launch_bounds__(256) void combine_many_kernel(CombineArgs A)
             }
         }
     }
-    combine_tail(A, run, s, dmax, pmax);
+    combine_tail<CLOCK>(A, run, s, dmax, pmax);
 }
 
 // 16-byte vector of T
@@ -273,7 +282,7 @@ struct Vec16<double> {
 // slot offsets come from a table already in summation order, so no load waits on another.  Each
 // wave folds its accumulators in a fixed tree and the wave totals are added pairwise in a fixed
 // tree: deterministic for a given slot count and NW.
-template <typename T, int NW>
+template <typename T, int NW, bool CLOCK>
 __global__ __launch_bounds__(64 * NW) void combine_vec_kernel(CombineArgs A)
 {
     using V4 = typename Vec16<T>::type;
@@ -282,7 +291,7 @@ __global__ __launch_bounds__(64 * NW) void combine_vec_kernel(CombineArgs A)
     static_assert(NW == 4 || NW == 8, "4 or 8 waves");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (A.mode == 0 && A.ctl->active == 0) return;
-    combine_clock(A);
+    combine_clock<CLOCK>(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -340,7 +349,7 @@ __global__ __launch_bounds__(64 * NW) void combine_vec_kernel(CombineArgs A)
         phi[ucell] = v;
         if (A.mode == 0) src[ucell] = fma(ssv, v, qv);
     }
-    combine_tail(A, run, s, dmax, pmax);
+    combine_tail<CLOCK>(A, run, s, dmax, pmax);
 }
 
 // The same for evenly spaced planes (the row-scan sweep's): a block's addresses come from one descriptor
@@ -361,7 +370,7 @@ __global__ __launch_bounds__(64 * NW) void combine_planes_kernel(CombineArgs A)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cells = D.cells, ns = D.nslots, s = D.sys;
     if (A.mode == 0 && A.ctl->active == 0) return;
-    combine_clock(A);
+    combine_clock<true>(A);
     const bool run = A.mode == 1 || A.nsys == 1 || A.sysctl[s].state == 0;
     __shared__ T wsum[NW][64 * V];
     double dmax = 0.0, pmax = 0.0;
@@ -412,7 +421,7 @@ __global__ __launch_bounds__(64 * NW) void combine_planes_kernel(CombineArgs A)
         phi[tid] = v;
         if (A.mode == 0) ((T*)A.src + D.src_off)[tid] = fma(ssv, v, qv);
     }
-    combine_tail(A, run, s, dmax, pmax);
+    combine_tail<true>(A, run, s, dmax, pmax);
 }
 
 // Large-tile combine with vector loads (at most 8 slots, e.g. ensembles with one lane group per
@@ -427,14 +436,14 @@ __global__ __launch_bounds__(64 * NW) void combine_planes_kernel(CombineArgs A)
 // 570 us a step, and these 4096-cell ones a quarter of that.
 constexpr int kFewTiles = 4;
 
-template <typename T>
+template <typename T, bool CLOCK>
 __global__ __launch_bounds__(256) void combine_vec_few_kernel(CombineArgs A)
 {
     using V4 = typename Vec16<T>::type;
     constexpr int V = 16 / sizeof(T);
     constexpr int TPB = kFewTiles;
     if (A.mode == 0 && A.ctl->active == 0) return;
-    combine_clock(A);
+    combine_clock<CLOCK>(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -502,7 +511,7 @@ __global__ __launch_bounds__(256) void combine_vec_few_kernel(CombineArgs A)
             if (A.mode == 0) *(V4*)(src + c0) = sn;
         }
     }
-    combine_tail(A, run, s, dmax, pmax);
+    combine_tail<CLOCK>(A, run, s, dmax, pmax);
 }
 
 // Combine of the linear-kernel sweep (four partial planes per slot: phi, Jx~, Jy~, phi~): per
@@ -510,12 +519,12 @@ __global__ __launch_bounds__(256) void combine_vec_few_kernel(CombineArgs A)
 // of the next sweep, S0 = sigma_s phi~ + q, S1 = sigma_s g Jx~, S2 = sigma_s g Jy~ (the folded
 // kernel 1 + g (c c' + s s') of eq. (2.1) contracted through its moments).  Without
 // normalization, or on a mirror-symmetric set, phi~ = phi and plane 3 is not formed.
-template <typename T>
+template <typename T, bool CLOCK>
 __global__ __launch_bounds__(256) void combine_moments_kernel(CombineArgs A)
 {
     const int tid = threadIdx.x;
     if (A.mode == 0 && A.ctl->active == 0) return;
-    combine_clock(A);
+    combine_clock<CLOCK>(A);
     const int2 blk = A.blocks[blockIdx.x];
     const int s = blk.x;
     const SystemDev& SD = A.sys[s];
@@ -586,7 +595,7 @@ __global__ __launch_bounds__(256) void combine_moments_kernel(CombineArgs A)
             }
         }
     }
-    combine_tail(A, run, s, dmax, pmax);
+    combine_tail<CLOCK>(A, run, s, dmax, pmax);
 }
 
 // Mark the start of a captured run of iterations (its first sweep is timed from here).
@@ -1255,25 +1264,26 @@ hipError_t launch_scan(const ScanArgs& a, int ntasks, int waves, bool fp64, int 
     return fp64 ? launch_scan_f64(a, ntasks, waves, G, C, inf, s) : launch_scan_f32(a, ntasks, waves, G, C, inf, s);
 }
 
-hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStream_t s)
+template <bool CLOCK>
+static hipError_t launch_combine_t(const CombineArgs& a, int nblocks, bool fp64, hipStream_t s)
 {
     if (a.nmom == 4) {
         if (a.many_cpt != 0) return hipErrorInvalidValue;
-        if (fp64) hipLaunchKernelGGL(combine_moments_kernel<double>, dim3(nblocks), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(combine_moments_kernel<float>, dim3(nblocks), dim3(256), 0, s, a);
+        if (fp64) hipLaunchKernelGGL((combine_moments_kernel<double, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((combine_moments_kernel<float, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
         return hipGetLastError();
     }
     if (a.nmom != 1) return hipErrorInvalidValue;
     if (a.vec == 2) {
         if (a.cells_per_block != kFewTiles * 256 * (fp64 ? 2 : 4)) return hipErrorInvalidValue;
-        if (fp64) hipLaunchKernelGGL(combine_vec_few_kernel<double>, dim3(nblocks), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(combine_vec_few_kernel<float>, dim3(nblocks), dim3(256), 0, s, a);
+        if (fp64) hipLaunchKernelGGL((combine_vec_few_kernel<double, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((combine_vec_few_kernel<float, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
         return hipGetLastError();
     }
     if (a.vec == 1 || a.vec == 3) {
         // 4 waves per block; 8 for systems of more than 64 slots
         if (a.cells_per_block != 64 * (fp64 ? 2 : 4)) return hipErrorInvalidValue;
-        if (a.pblocks) {
+        if (CLOCK && a.pblocks) {   // the row-scan sweep's planes
             if (a.vec == 3) {
                 if (fp64) hipLaunchKernelGGL((combine_planes_kernel<double, 8>), dim3(nblocks), dim3(512), 0, s, a);
                 else hipLaunchKernelGGL((combine_planes_kernel<float, 8>), dim3(nblocks), dim3(512), 0, s, a);
@@ -1282,11 +1292,11 @@ hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStrea
                 else hipLaunchKernelGGL((combine_planes_kernel<float, 4>), dim3(nblocks), dim3(256), 0, s, a);
             }
         } else if (a.vec == 3) {
-            if (fp64) hipLaunchKernelGGL((combine_vec_kernel<double, 8>), dim3(nblocks), dim3(512), 0, s, a);
-            else hipLaunchKernelGGL((combine_vec_kernel<float, 8>), dim3(nblocks), dim3(512), 0, s, a);
+            if (fp64) hipLaunchKernelGGL((combine_vec_kernel<double, 8, CLOCK>), dim3(nblocks), dim3(512), 0, s, a);
+            else hipLaunchKernelGGL((combine_vec_kernel<float, 8, CLOCK>), dim3(nblocks), dim3(512), 0, s, a);
         } else {
-            if (fp64) hipLaunchKernelGGL((combine_vec_kernel<double, 4>), dim3(nblocks), dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((combine_vec_kernel<float, 4>), dim3(nblocks), dim3(256), 0, s, a);
+            if (fp64) hipLaunchKernelGGL((combine_vec_kernel<double, 4, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+            else hipLaunchKernelGGL((combine_vec_kernel<float, 4, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
         }
         return hipGetLastError();
     }
@@ -1295,25 +1305,30 @@ hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStrea
         // block tiles of 64 * many_cpt cells (cells_per_block must match)
         if (a.cells_per_block != 64 * a.many_cpt) return hipErrorInvalidValue;
         if (fp64) {
-            if (a.many_cpt == 1) hipLaunchKernelGGL((combine_many_kernel<double, 1>), dim3(nblocks), dim3(256), 0, s, a);
-            else if (a.many_cpt == 2) hipLaunchKernelGGL((combine_many_kernel<double, 2>), dim3(nblocks), dim3(256), 0, s, a);
-            else if (a.many_cpt == 4) hipLaunchKernelGGL((combine_many_kernel<double, 4>), dim3(nblocks), dim3(256), 0, s, a);
-            else if (a.many_cpt == 8) hipLaunchKernelGGL((combine_many_kernel<double, 8>), dim3(nblocks), dim3(256), 0, s, a);
+            if (a.many_cpt == 1) hipLaunchKernelGGL((combine_many_kernel<double, 1, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+            else if (a.many_cpt == 2) hipLaunchKernelGGL((combine_many_kernel<double, 2, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+            else if (a.many_cpt == 4) hipLaunchKernelGGL((combine_many_kernel<double, 4, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+            else if (a.many_cpt == 8) hipLaunchKernelGGL((combine_many_kernel<double, 8, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
             else return hipErrorInvalidValue;
         } else {
-            if (a.many_cpt == 1) hipLaunchKernelGGL((combine_many_kernel<float, 1>), dim3(nblocks), dim3(256), 0, s, a);
-            else if (a.many_cpt == 2) hipLaunchKernelGGL((combine_many_kernel<float, 2>), dim3(nblocks), dim3(256), 0, s, a);
-            else if (a.many_cpt == 4) hipLaunchKernelGGL((combine_many_kernel<float, 4>), dim3(nblocks), dim3(256), 0, s, a);
-            else if (a.many_cpt == 8) hipLaunchKernelGGL((combine_many_kernel<float, 8>), dim3(nblocks), dim3(256), 0, s, a);
+            if (a.many_cpt == 1) hipLaunchKernelGGL((combine_many_kernel<float, 1, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+            else if (a.many_cpt == 2) hipLaunchKernelGGL((combine_many_kernel<float, 2, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+            else if (a.many_cpt == 4) hipLaunchKernelGGL((combine_many_kernel<float, 4, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
+            else if (a.many_cpt == 8) hipLaunchKernelGGL((combine_many_kernel<float, 8, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
             else return hipErrorInvalidValue;
         }
         return hipGetLastError();
     }
     if (fp64)
-        hipLaunchKernelGGL(combine_kernel<double>, dim3(nblocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((combine_kernel<double, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL(combine_kernel<float>, dim3(nblocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((combine_kernel<float, CLOCK>), dim3(nblocks), dim3(256), 0, s, a);
     return hipGetLastError();
+}
+
+hipError_t launch_combine(const CombineArgs& a, int nblocks, bool fp64, hipStream_t s)
+{
+    return a.clock ? launch_combine_t<true>(a, nblocks, fp64, s) : launch_combine_t<false>(a, nblocks, fp64, s);
 }
 
 hipError_t launch_sweep_prologue(Ctl* ctl, hipStream_t s)
