@@ -109,8 +109,12 @@ struct DevMem {
             return hipSuccess;
         }
         hipError_t e = hipMalloc(&p, n);
-        if (e == hipSuccess) bytes = n;
-        else p = nullptr;
+        if (e == hipSuccess) {
+            bytes = n;
+        } else {
+            p = nullptr;
+            (void)hipGetLastError();  // reported here, not again by the next launch
+        }
         return e;
     }
     template <typename T>
@@ -2555,6 +2559,40 @@ bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smod
     return take(4, 64);
 }
 
+// The rule's choice for a solve whose options leave sweep kernel and shape open.
+bool row_scan_choice(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smode, TuneChoice& pick)
+{
+    // a caller who names rows or ordinates per lane asks for those among the other kernels' shapes
+    return o.tile_x == 0 && o.band == 0 && o.diag_rows == 0 && o.diag_k == 0 && autotune_enabled() && scan_rule(in, o, smode, pick);
+}
+
+// Device bytes of a system's partial planes in a row-scan shape, at most: one plane per workgroup's ordinates and
+// what is left of each quadrant.
+int64_t scan_plane_bytes(const TuneChoice& c, const RuleSystem& s, bool fp64, int smode)
+{
+    int per = c.band * (c.rows > 0 ? kWave / c.rows : 1);
+    if (c.band > kScanWaves) {
+        const ScanShape sh = scan_class_shape(scan_class(s.nx));
+        per = c.band / sh.strips * (kWave / sh.G * sh.K);
+    }
+    return (s.n / per + 4) * ang_plane((int64_t)s.nx * s.ny * (smode == 1 ? 4 : 1)) * (fp64 ? 8 : 4);
+}
+
+// Samples of an ensemble solved at once: as many as a 24 GiB budget and 1024 allow, with per_sample bytes each and,
+// on the row-scan sweep, their partial planes (whose shape goes by how many there are).
+int ensemble_batch(const RuleSystem& s, int t, int64_t per_sample, const rom_si_opts& o, int smode)
+{
+    const int64_t budget = (int64_t)24 << 30;
+    auto fit = [&](int64_t bytes) { return std::max<int64_t>(1, budget / std::max<int64_t>(bytes, 1)); };
+    int64_t B = std::min<int64_t>({(int64_t)t, fit(per_sample), 1024});
+    for (TuneChoice c; B > 1 && row_scan_choice(std::vector<RuleSystem>(B, s), o, smode, c);) {
+        const int64_t most = fit(per_sample + scan_plane_bytes(c, s, o.precision == ROM_PREC_FP64, smode));
+        if (most >= B) break;
+        B = most;
+    }
+    return (int)B;
+}
+
 // Whether one sweep with a shared source takes the row-scan sweep (160 x 120, 96 ordinates: a call 133 us, 316 on the
 // strip kernel, whose sweep alone is 152): the rule of the solves, for plans of up to 16 MiB.  Within
 // that the strip kernel's plan, too, fits the region of rom_sweep_noalloc, so no call is accepted or
@@ -2675,17 +2713,33 @@ int solve_systems(rom_handle* owner, std::vector<SysInput>& in, const rom_si_opt
     if (reuse == 0 || !slot) {
         const bool free_shape = o.sweep == ROM_SWEEP_DIAG ? (o.diag_rows == 0 || o.diag_k == 0 || o.band == 0)
                                                           : (o.tile_x == 0 && o.band == 0);
+        const bool measured = free_shape && autotune_enabled();
+        auto build = [&] {
+            slot.reset(new Plan());
+            build_plan(*slot, in, o, smode, o.max_iter);
+            if (aniso) {
+                build_kernel_matrices(*slot, in, owner->stream());
+                build_contract_batch(*slot);
+            }
+        };
         TuneChoice scan;
-        if (free_shape && autotune_enabled()) {
-            // a caller who names rows or ordinates per lane asks for those among the other kernels' shapes
-            if (o.diag_rows == 0 && o.diag_k == 0 && scan_rule(rule_systems(in), o, smode, scan)) apply_choice(scan, o);
-            else autotune(owner, in, o, smode, owner->stream());
+        bool built = false;
+        if (row_scan_choice(rule_systems(in), o, smode, scan)) {
+            apply_choice(scan, o);
+            try {
+                build();
+                built = true;
+            } catch (const Fail& f) {
+                // the row-scan sweep holds a partial plane per few ordinates: where they do not fit, the other
+                // kernels' may (a sixteenth of them and less)
+                if (f.code != ROM_E_NOMEM) throw;
+                slot.reset();
+                o = o_in;
+            }
         }
-        slot.reset(new Plan());
-        build_plan(*slot, in, o, smode, o.max_iter);
-        if (aniso) {
-            build_kernel_matrices(*slot, in, owner->stream());
-            build_contract_batch(*slot);
+        if (!built) {
+            if (measured) autotune(owner, in, o, smode, owner->stream());
+            build();
         }
     }
     res = run_si(*slot, owner->stream(), o);
@@ -2727,7 +2781,7 @@ int check_ensemble(rom_handle* h, const rom_ord_spec& spec, const rom_si_opts* o
 }
 
 // Samples first .. first + t - 1 of (spec, seed), generated exactly as rom_generate_ordinates
-// does, solved in batches (as many samples per launch as a 24 GiB budget and 1024 allow) with
+// does, solved in batches (as many samples per launch as ensemble_batch allows) with
 // one cached plan per batch shape, refreshed with each batch's ordinates.  After each batch,
 // per_batch(plan, index of the batch's first sample in this call, batch size) consumes the
 // fluxes while they are on the device.
@@ -2738,9 +2792,7 @@ int ensemble_batches(rom_handle* h, int64_t first, int t, uint64_t seed, const r
     const bool aniso = is_aniso(h);
     const int64_t per_sample = h->cells * (int64_t)(aniso ? (n + 128) * 6 : 0) + h->cells * 8 * 8 +
                                (int64_t)h->grid.nx * h->grid.ny / 2 * 4;
-    const int64_t budget = (int64_t)24 << 30;
-    int B = (int)std::max<int64_t>(1, std::min<int64_t>(t, budget / std::max<int64_t>(per_sample, 1)));
-    B = std::min(B, 1024);
+    const int B = ensemble_batch(rule_systems({{h, nullptr, nullptr, n, false}})[0], t, per_sample, o, scat_mode(h));
     std::vector<double> dirs((size_t)t * 3 * n), w((size_t)t * n);
     for (int smp = 0; smp < t; ++smp) {
         const int rc = generate_ordinates(spec, seed, first + smp, dirs.data() + (size_t)smp * 3 * n, w.data() + (size_t)smp * n);
@@ -2807,6 +2859,21 @@ int rom_scan_rule(const int64_t* systems, int32_t count, int32_t precision, int3
     shape[1] = c.rows;
     shape[2] = c.tx;
     return 1;
+}
+
+// Samples of an ensemble of {nx, ny, ordinates, row changes} solved at once, and in *bytes what they hold: per_sample
+// each and the partial planes of the row-scan sweep.  For the tests, as above.
+int rom_ensemble_batch_size(const int64_t* system, int32_t t, int64_t per_sample, int32_t precision, int32_t smode, int64_t* bytes)
+{
+    const RuleSystem s{(int)system[0], (int)system[1], (int)system[2], system[3], 0.0};
+    rom_si_opts o;
+    std::memset(&o, 0, sizeof(o));
+    o.precision = precision;
+    const int B = ensemble_batch(s, t, per_sample, o, smode);
+    TuneChoice c;
+    *bytes = B * (per_sample + (row_scan_choice(std::vector<RuleSystem>(B, s), o, smode, c)
+                                    ? scan_plane_bytes(c, s, precision == ROM_PREC_FP64, smode) : 0));
+    return B;
 }
 
 int rom_source_iterate(rom_handle* h, const rom_si_opts* opts, double* phi, rom_si_stats* stats)

@@ -437,3 +437,54 @@ def test_sources_near_the_end_of_fp32(R, orc, kernel, dd, top, where):
     ref = orc.source_iterate(orc.Problem(nx, ny, one, 0.5 * one, q, inflow=infl, inflow_angular=ang), d, w, W, tol=-1, max_iter=6,
                              scheme=orc.SCHEME_DD if dd else orc.SCHEME_STEP)["phi"]
     parity.check(phi, ref, 1e-5)
+
+
+@pytest.mark.parametrize("kernel,prec", [("iso", "fp64"), ("linear", "fp32")])
+def test_partial_planes_that_do_not_fit(R, orc, kernel, prec):
+    """Where the allocator has no room for the row scan's partial planes, the solve runs on another kernel, which needs
+    a part of them, and a later solve with room takes the row scan."""
+    import torch
+    nx, ny, n = 200, 180, 256
+    f = problem(np.random.default_rng(2), nx, ny, "uniform")
+    d, w = R.generate_ordinates(R.ROM_ORD_STRATIFIED, 8, 8, seed=1)
+    cells, planes = nx * ny, 64 * (4 if kernel == "linear" else 1)
+    limit = cells * planes * (8 if prec == "fp64" else 4) // 2   # half of the planes (of 4 ordinates)
+    R._default_allocator()
+    give, back = R._allocator
+    refused = []
+
+    def alloc(nbytes, ctx):
+        if nbytes > limit:
+            refused.append(nbytes)
+            return None
+        return give(nbytes, ctx)
+
+    def free(p, ctx):
+        back(p, ctx)
+
+    cbs = (R._ALLOC_FN(alloc), R._FREE_FN(free))
+    W = None if kernel == "iso" else orc.build_W(d, w, orc.SCAT_LINEAR, 0.6, fold=1)
+    ref = orc.source_iterate(orc.Problem(nx, ny, *f), d, w, W, tol=-1, max_iter=3)["phi"]
+    o = R.si_opts(tol=-1, max_iter=3, precision=R.ROM_PREC_FP64 if prec == "fp64" else R.ROM_PREC_FP32)
+
+    def solve():
+        h = R.Handle(nx, ny, *f)
+        h.set_ordinates(d, w)
+        if kernel != "iso":
+            h.set_scattering(R.ROM_SCAT_LINEAR, 0.6)
+        phi, s, _ = h.source_iterate(o)
+        h.close()
+        return phi, s
+
+    bar = 1e-11 if prec == "fp64" else 1e-5
+    assert R.lib().rom_set_allocator(cbs[0], cbs[1], None) == R.ROM_OK
+    try:
+        phi, s = solve()
+    finally:
+        R.use_torch_allocator()
+    assert refused and s.lanes != 1
+    parity.check(phi, ref, bar)
+    torch.cuda.synchronize()
+    phi, s = solve()
+    assert s.lanes == 1
+    parity.check(phi, ref, bar)

@@ -98,3 +98,24 @@ def test_media_that_change_from_row_to_row(R, prec, nx, ny, changes, taken):
     assert (choice(R, [(nx, ny, 64, changes)] * 3, prec) is not None) == taken
     assert choice(R, [(nx, ny, 64, 0)], prec) is not None
     assert choice(R, [(nx, ny, 64, changes)], prec, dd=True) is not None   # the strip kernel is slower there in any medium
+
+
+# The samples that an ensemble solves at once fit its 24 GiB with the row scan's partial planes, whose number follows
+# from the shape that the rule takes for as many of them.
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("mode", [ISO, LINEAR])
+@pytest.mark.parametrize("nx,n,t", [(64, 64, 16), (512, 256, 1000), (512, 128, 64), (256, 128, 1024), (500, 1024, 300), (100, 16, 5000)])
+def test_ensemble_batches_fit_their_budget(R, nx, n, t, mode, prec):
+    per_sample = nx * nx * 66
+    f = R.lib().rom_ensemble_batch_size
+    s = np.array([nx, nx, n, 0], dtype=np.int64)
+    held = C.c_int64()
+    B = f(C.c_void_p(s.ctypes.data), t, C.c_int64(per_sample), R.ROM_PREC_FP64 if prec == "fp64" else R.ROM_PREC_FP32, mode, C.byref(held))
+    assert 1 <= B <= min(t, 1024)
+    assert held.value <= 24 << 30
+    took = choice(R, [(nx, nx, n)] * B, prec, mode)
+    if took is not None and took[0] <= 4:   # a plane per workgroup: its wavefronts' ordinates
+        planes = n // (took[0] * 64 // took[1])
+        assert B * (per_sample + planes * nx * nx * (4 if mode == LINEAR else 1) * (8 if prec == "fp64" else 4)) <= 24 << 30
+    if t * per_sample < 1 << 30:   # small ones are not split
+        assert B == min(t, 1024)
