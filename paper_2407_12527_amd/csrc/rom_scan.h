@@ -416,7 +416,7 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
 
     T a[K], b[K], w[K], lc[KM], ls[KM];
     ScanB even[sizeof(T) == 4 ? K : 1];   // FP32: b[k] is the current rows' value
-    uint32_t phase = 0;
+    uint32_t phase = (uint32_t)(strip * 64 + lane) * 0xc13fa9a9u;   // neighbours in a row are out of step
     T y[K][C], rr[K][C], A[K][C], m[K][NS];
     T X[DD ? K : 1][DD ? C : 1];   // diamond difference: the x-face multiplier 2 A - 1, without its cancellation
 #pragma unroll
