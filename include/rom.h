@@ -81,9 +81,11 @@ extern "C" {
  * (every scheme, source kind and angular-flux output).  DIAG: grid rows on lanes, each
  * wavefront sweeping the anti-diagonals of a 16- or 64-row block with the y-face value passed one
  * lane up; far more parallel work per ordinate, for isotropic step-scheme source iteration.  With
- * AUTO librom may also take a third kernel, which sweeps whole rows as prefix scans (sources from the
- * scalar flux or the linear kernel's moments, nx <= 1024); it reports itself with lanes = 1, as
- * ROM_SWEEP_DIAG where that kernel applies and as ROM_SWEEP_STRIP elsewhere. */
+ * AUTO librom may also take a third kernel, which sweeps whole rows as prefix scans (isotropic step
+ * sweeps up to nx = 1024; the linear kernel, diamond difference and, with the step scheme, dense kernels
+ * up to 512).  No option asks for it: it follows from sizes and media, reports itself with lanes = 1,
+ * as ROM_SWEEP_DIAG where that kernel applies and as ROM_SWEEP_STRIP elsewhere, and its reported shape, given
+ * back as options, asks for those kernels. */
 #define ROM_SWEEP_AUTO 0
 #define ROM_SWEEP_STRIP 1
 #define ROM_SWEEP_DIAG 2
@@ -147,8 +149,9 @@ typedef struct {
                               clock */
     int32_t sweeps;        /* sweep launches that did work */
     int32_t tile_x, tile_y;/* strip sweep: chunk x strip shape; row-lane sweep: ordinates per lane
-                              and rows per lane block (set or autotuned) */
-    int32_t band;          /* strips (strip sweep) or wavefronts (row-lane sweep) per workgroup */
+                              and rows per lane block (set or autotuned); row-scan sweep: ordinates per
+                              lane group and lanes per group, of this problem */
+    int32_t band;          /* strips (strip sweep) or wavefronts (the others) per workgroup */
     int32_t lanes;         /* strip sweep: lanes per ordinate group (16, 32 or 64); row-lane sweep: rows
                               per lane block; row-scan sweep: 1 */
     int32_t sweep;         /* ROM_SWEEP_STRIP or ROM_SWEEP_DIAG */

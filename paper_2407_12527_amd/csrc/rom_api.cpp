@@ -1849,7 +1849,7 @@ SolveResult run_si(Plan& P, hipStream_t s, const rom_si_opts& o)
         // reported among the row-lane sweeps, or the strip sweeps where those do not apply
         r.kind = P.nmom == 1 && !P.dd && !(P.aniso && P.fp64) ? ROM_SWEEP_DIAG : ROM_SWEEP_STRIP;
         r.tx = P.scan_shape(0).K;
-        r.ty = P.scan_shape(0).G == 16 ? 16 : 64;
+        r.ty = P.scan_shape(0).G;
         r.band = P.sW;
         r.lanes = 1;
     } else if (P.kind == ROM_SWEEP_DIAG) {
@@ -2976,8 +2976,9 @@ int rom_solve_batch(rom_handle* const* hs, int32_t k, const rom_si_opts* opts, d
                 stats[i].device_ms = res.ms;
                 stats[i].sweep_ms = res.sweep_ms;
                 stats[i].sweeps = res.sweeps;
-                stats[i].tile_x = res.tx;
-                stats[i].tile_y = res.ty;
+                const ScanShape sh = P->kind == kSweepScan ? P->scan_shape(P->sys[i].prob) : ScanShape{};
+                stats[i].tile_x = P->kind == kSweepScan ? sh.K : res.tx;
+                stats[i].tile_y = P->kind == kSweepScan ? sh.G : res.ty;
                 stats[i].band = res.band;
                 stats[i].lanes = res.lanes;
                 stats[i].sweep = res.kind;

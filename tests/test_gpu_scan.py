@@ -488,3 +488,20 @@ def test_partial_planes_that_do_not_fit(R, orc, kernel, prec):
     phi, s = solve()
     assert s.lanes == 1
     parity.check(phi, ref, bar)
+
+
+def test_reported_shapes(R, monkeypatch):
+    """Each problem of a batch reports the shape of its own width: lanes per row in tile_y, ordinates per group in tile_x."""
+    monkeypatch.setenv("ROM_SWEEP_SCAN", "2")   # the first width beyond 128: the form for full GPUs
+    hs = []
+    for nx in (700, 40, 100, 200, 350, 512):
+        st = np.ones(nx * 8)
+        h = R.Handle(nx, 8, st, 0.5 * st, st)
+        h.set_ordinates(*R.generate_ordinates(R.ROM_ORD_IID_SPHERE, 12, seed=1))
+        hs.append(h)
+    o = R.si_opts(tol=-1, max_iter=2)
+    stats = R.solve_batch(hs, o)[1]
+    assert all(s.lanes == 1 and s.band == 8 for s in stats)
+    assert [(s.tile_y, s.tile_x) for s in stats] == [(64, 2), (16, 4), (16, 2), (32, 2), (64, 2), (64, 2)]
+    s = hs[3].source_iterate(o)[1]
+    assert (s.lanes, s.band, s.tile_y, s.tile_x) == (1, 8, 32, 2)
