@@ -2463,7 +2463,9 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 //   * not that form for hundreds of small samples of 64 ordinates or fewer, whose quadrants leave most of a
 //     workgroup's eight wavefronts idle: up to 64 columns any (64^2, 256 samples of 64: 77 us against 67; 512 of
 //     32: 156 / 89), up to 128 columns more than 300 (128^2, 512 samples of 32: 303 / 261; 256 of them 145 / 177).
-bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smode, TuneChoice& pick)
+// alone: a single sweep, whose other kernel is the strip kernel (64^2 cells, 16 ordinates: 84 us a sweep, the row
+// scan 28 with a random sigma_t), so that the lines against the row-lane kernel in such media are not its.
+bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smode, TuneChoice& pick, bool alone = false)
 {
     if (o.sweep != ROM_SWEEP_AUTO || (smode == 2 && o.scheme == ROM_SCHEME_DD)) return false;
     const bool fp64 = o.precision == ROM_PREC_FP64, dd = o.scheme == ROM_SCHEME_DD;
@@ -2543,7 +2545,8 @@ bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smod
         pick = c[0];
         return maxnx <= 512 && changes * 4 <= rows;
     }
-    if (fp64 && maxnx <= 64 ? changes * 4 > rows && 5 * maxnx <= maxny + 60
+    if (alone ? maxnx > 64 && changes * 4 > rows
+        : fp64 && maxnx <= 64 ? changes * 4 > rows && 5 * maxnx <= maxny + 60
         : fp64 || maxnx > 128 ? changes * 4 > rows
                               : changes * 5 > rows && changes > 32 * (int64_t)in.size())
         return false;
@@ -2601,7 +2604,7 @@ bool single_sweep_by_scan(const std::vector<SysInput>& in, rom_si_opts& o)
 {
     if (o.scheme != ROM_SCHEME_STEP || o.tile_x != 0 || o.tile_y != 0 || o.band != 0 || o.diag_rows != 0 || o.diag_k != 0) return false;
     TuneChoice pick;
-    if (!scan_rule(rule_systems(in), o, 0, pick) || pick.band > kScanWaves) return false;
+    if (!scan_rule(rule_systems(in), o, 0, pick, true) || pick.band > kScanWaves) return false;
     const rom_handle* h = in[0].h;
     const int64_t n = in[0].n, rows = h->grid.ny + 2 * kScanAhead;
     const int64_t inflow = (n + 64) * (rows + 1024);   // of the entry faces, at most
@@ -2843,7 +2846,8 @@ extern "C" {
 
 // The rule's choice for `count` systems of {nx, ny, ordinates, row changes} in shape[0..2]: wavefronts, lanes
 // per row and cells per lane (zero in the form for full GPUs); returns 0 where it leaves them to the
-// other kernels.  Host arithmetic, not part of the interface: the tests ask it about sizes that no test can run.
+// other kernels (smode -1: a single sweep).  Host arithmetic, not part of the interface: the tests ask it about
+// sizes that no test can run.
 int rom_scan_rule(const int64_t* systems, int32_t count, int32_t precision, int32_t scheme, int32_t smode, int32_t* shape)
 {
     std::vector<RuleSystem> in;
@@ -2854,7 +2858,7 @@ int rom_scan_rule(const int64_t* systems, int32_t count, int32_t precision, int3
     o.precision = precision;
     o.scheme = scheme;
     TuneChoice c;
-    if (!scan_rule(in, o, smode, c)) return 0;
+    if (!scan_rule(in, o, std::max(smode, 0), c, smode < 0)) return 0;
     shape[0] = c.band;
     shape[1] = c.rows;
     shape[2] = c.tx;

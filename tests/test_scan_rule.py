@@ -4,7 +4,7 @@ import ctypes as C
 import numpy as np
 import pytest
 
-ISO, LINEAR, DENSE = 0, 1, 2
+ISO, LINEAR, DENSE, SINGLE = 0, 1, 2, -1
 
 
 @pytest.fixture(scope="module")
@@ -98,6 +98,8 @@ def test_media_that_change_from_row_to_row(R, prec, nx, ny, changes, taken):
     assert (choice(R, [(nx, ny, 64, changes)] * 3, prec) is not None) == taken
     assert choice(R, [(nx, ny, 64, 0)], prec) is not None
     assert choice(R, [(nx, ny, 64, changes)], prec, dd=True) is not None   # the strip kernel is slower there in any medium
+    if nx <= 64:
+        assert choice(R, [(nx, ny, 64, changes)], prec, SINGLE) is not None   # and it is the other one for single sweeps
 
 
 # The samples that an ensemble solves at once fit its 24 GiB with the row scan's partial planes, whose number follows
