@@ -2442,7 +2442,10 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 //     samples of 64: 23 us against 27; 128^2 the same: 43 / 54; 64^2 x 80: 24 / 19);
 //   * batches of uneven grids below that give every grid the lanes of the widest: measured instead where
 //     their widths add up to more than 2800 (19 problems, mean width 330: 4.45 ms a solve against 4.04 on
-//     the row-lane kernel; 13 x 264: 3.75 / 3.21; but 11 x 226: 3.63 / 4.34; 10 x 179: 3.57 / 4.41);
+//     the row-lane kernel; 13 x 264: 3.75 / 3.21; but 11 x 226: 3.63 / 4.34; 10 x 179: 3.57 / 4.41), and where the
+//     tallest is not the widest: its rows take what the widest's cells per lane (C) cost, 0.15 us + 0.011 C (FP64
+//     0.13 + 0.03 C), the row-lane kernel 0.1 us per row and column of each, 0.15 beyond 64 rows (FP64 twice that;
+//     480 x 34 with 32 x 292, 64 ordinates: 79 / 54 us a step, FP64 121 / 103; 224 x 386 with 102 x 113: 76 / 132);
 //   * the linear kernel up to the ordinates where the combine's sum over their moment planes, one plane
 //     per four ordinates (16 on 16-lane groups), takes longer than the strip kernel's way through the grid
 //     (FP32: 16 us + 0.036 per ordinate + 0.2 per row against 8 + 0.65 per row and column, FP64 18 + 0.044 + 0.3
@@ -2557,6 +2560,14 @@ bool scan_rule(const std::vector<RuleSystem>& in, const rom_si_opts& o, int smod
     if (!fp64 && ords >= (maxnx <= 64 ? 16384 : maxnx <= 128 ? 4096 : 2048))
         return take(maxnx > 256 && ords >= 6144 && sixteen ? 16 : 8, 0);
     if (2 * minnx <= maxnx && widths > 2800) return false;
+    if (2 * minnx <= maxnx) {
+        double scan = 0.0, lane = 0.0;
+        for (auto& s : in) {
+            scan = std::max(scan, s.ny * (fp64 ? 0.13 + 0.03 * c[0].tx : 0.15 + 0.011 * c[0].tx));
+            lane = std::max(lane, (s.nx + s.ny) * (s.ny > 64 ? 0.15 : 0.1) * (fp64 ? 2 : 1));
+        }
+        if (scan > lane) return false;
+    }
     if (maxnx <= 64 && (ords >= (fp64 ? 1024 : 2048) || (!fp64 && maxn >= 256 && maxny <= 100))) return take(4, 16);
     if (maxnx <= 128 && maxnx > 64 && (fp64 ? ords >= 4096 || (ords >= 2048 && maxny <= 128) : ords >= 2048)) return take(4, 16);
     return take(4, 64);

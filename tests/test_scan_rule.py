@@ -121,3 +121,12 @@ def test_ensemble_batches_fit_their_budget(R, nx, n, t, mode, prec):
         assert B * (per_sample + planes * nx * nx * (4 if mode == LINEAR else 1) * (8 if prec == "fp64" else 4)) <= 24 << 30
     if t * per_sample < 1 << 30:   # small ones are not split
         assert B == min(t, 1024)
+
+
+# Batches of uneven grids on the lanes of the widest: not where a narrow one is so tall that its rows cost more than
+# the row-lane kernel's way through it.
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("grids,taken", [([(480, 34), (32, 292)], False), ([(480, 300), (32, 292)], True),
+                                         ([(224, 386), (102, 113)], True), ([(480, 34), (300, 292)], True), ([(32, 292)], True)])
+def test_batches_of_uneven_grids(R, prec, grids, taken):
+    assert (choice(R, [(nx, ny, 64) for nx, ny in grids], prec) is not None) == taken
