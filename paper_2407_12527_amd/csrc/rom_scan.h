@@ -29,7 +29,7 @@
 // Dense kernels (MODE 2) keep a plane of cells per ordinate, so a wavefront's source rows are as
 // contiguous as an isotropic source's; the weighted angular flux leaves from the exchange, where all of a
 // workgroup's ordinates of a cell meet.  Bound by memory: 256^2, 1024 ordinates, FP32, reads 256 MB and
-// writes 192 MB in 84 us (5.3 TB/s; the row-lane sweep on ordinate blocks took 293 us, eight wavefronts
+// writes 192 MB in 78 us (5.7 TB/s; the row-lane sweep on ordinate blocks took 293 us, eight wavefronts
 // per workgroup, on half the CUs, 128 us); FP64 96 x 80, 20 us (strip sweep 232).
 #pragma once
 #include "rom_common.h"
@@ -260,8 +260,10 @@ __device__ __forceinline__ float scan_rcp(float sg, float kap, float klo)
 //   * along a row, A and X are rounded with a dither that runs evenly through +- half an ulp over the
 //     cells (u), so that their mean over a row is the exact value to a fraction of that;
 //   * from row to row the flux goes by b r in one column, which a dither over columns would leave with
-//     one error for good (16 x 1000 cells: 1.2e-5 of phi).  r is rounded to nearest, and b takes one of
-//     two neighbouring values by rows, so that its mean makes up for r (3.5e-6; scan_even).
+//     one error for good (one ordinate along 1000 rows: 6.9e-5 of phi; row-lane sweep 2.2e-5).  r is
+//     rounded to nearest, and b takes one of two neighbouring values by rows, so that its mean makes
+//     up for r (1.7e-6; scan_even).  Neighbouring lanes take them in different rows, so that a flux across
+//     columns does not meet the same share of them in each.
 // The steps' own roundings remain.  `rho` is the relative rounding error of r, 1 / (r d) - 1.
 __device__ __forceinline__ float ulp_of(float x) { return __uint_as_float(__float_as_uint(x) & 0x7f800000u) * 0x1p-23f; }
 template <bool DD>
@@ -292,6 +294,9 @@ __device__ __forceinline__ void scan_coefficients(double sg, double kap, double,
 
 // The two values of an ordinate's b in a lane: `lo`, and the next one up in a fraction `part` / 2^32 of
 // the rows, with the mean b (1 + rho).  The lowest bit of `part` keeps which of the two b itself is.
+// A medium of kScanEven rows or fewer has one value anyway and takes b itself (24 x 200 cells with a change
+// in every row: a step of 64 us, 80 with the work for two values).
+constexpr int kScanEven = 4;   // rows that share a value of b
 struct ScanB {
     uint32_t lo, part;
     __device__ __forceinline__ float own() const { return __uint_as_float(lo + (part & 1)); }
@@ -340,7 +345,6 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* scalar_ptr
     return (const __attribute__((address_space(4))) T*)p;
 }
 
-constexpr int kScanEven = 4;   // rows that share a value of b
 
 // Everything one task needs (uniform values).
 template <typename T>
@@ -433,8 +437,8 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
 #pragma unroll
         for (int c = 0; c < C; ++c) y[k][c] = (INF && yin) ? yin[((g * K + k) * SPLIT + strip) * (G * C) + pos * C + c] : T(0);
     }
-    // multipliers of a row from its sigma_t
-    auto coefficients = [&](const T (&sg)[C]) {
+    // multipliers of a row from its sigma_t, which `rows` rows have
+    auto coefficients = [&](const T (&sg)[C], const int rows) {
         const bool whole = (strip * G + pos + 1) * C <= nx;   // no cell past the row's end
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -455,7 +459,8 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
                 err += rho;
             }
             if constexpr (sizeof(T) == 4) {
-                even[k] = scan_even(bk, whole ? err * (1.0f / C) : err0);   // the lane's cells in the mean
+                even[k] = ScanB{__float_as_uint(bk), 0};
+                if (rows > kScanEven) even[k] = scan_even(bk, whole ? err * (1.0f / C) : err0);   // the lane's cells in the mean
                 b[k] = even[k].at(phase);
             }
             scan_multipliers<T, G>(p, lane, m[k]);
@@ -486,7 +491,9 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
             xoff += xstep;
         }
     };
-    int nc = 0;   // next row whose multipliers differ (row 0 first)
+    int nc = 0;   // next row whose multipliers differ (row 0 first), in FP32 also the one after it
+    int nn = 0;
+    if constexpr (sizeof(T) == 4) nn = scalar_ptr(D.next)[0];
     if constexpr (AHEAD) run_load<T, C>(stbase, off0, sg);
 #pragma unroll
     for (int u = 0; u < U; ++u) fetch(u);
@@ -664,6 +671,7 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
         }
         pbase += U * step;
     };
+    if constexpr (sizeof(T) == 4) asm volatile("" : : "s"(nn));
     const int batches = (ny + U - 1) / U + SPLIT - 1;
     for (int bi = 0, jb = 0; bi < batches; ++bi, jb += U) {
         T* const buf = lds + (bi & 1) * U * ROW;
@@ -695,14 +703,18 @@ __device__ __forceinline__ void scan_rows(const ScanTask<T>& D, T* lds, const in
                 }
                 if (__builtin_expect(jj == nc, 0)) {
                     if constexpr (AHEAD) {
-                        coefficients(sg);
-                        nc = scalar_ptr(D.next)[jj];
-                        run_load<T, C>(stbase, off0 + (uint32_t)min(nc, ny - 1) * dstep, sg);
+                        coefficients(sg, nn - jj);
                     } else {
                         T now[C];
                         run_load<T, C>(stbase, off0 + (uint32_t)jj * dstep, now);
-                        coefficients(now);
-                        nc = scalar_ptr(D.next)[jj];
+                        coefficients(now, nn - jj);
+                    }
+                    if constexpr (sizeof(T) == 4) nc = nn;
+                    else nc = scalar_ptr(D.next)[jj];
+                    if constexpr (AHEAD) run_load<T, C>(stbase, off0 + (uint32_t)min(nc, ny - 1) * dstep, sg);
+                    if constexpr (sizeof(T) == 4) {
+                        nn = scalar_ptr(D.next)[min(nc, ny - 1)];
+                        asm volatile("" : : "s"(nn));   // waited for here: outstanding, it would be so at every LDS wait
                     }
                 }
                 T t[K][C], bt[K], x[K];
