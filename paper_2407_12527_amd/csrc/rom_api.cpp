@@ -1867,7 +1867,7 @@ SolveResult run_si(Plan& P, hipStream_t s, const rom_si_opts& o)
 }
 
 // The scalar fluxes of systems 0 to count - 1 of one problem, [count][cells]: they lie one after the other,
-// so one copy (192 samples of 100^2 in FP64: 192 copies took 2.1 ms of a 4.6 ms call).
+// so one copy (192 samples of 100^2 in FP64: 192 copies took 1.5 ms of a 4.6 ms call).
 void download_samples(const Plan& P, int count, double* out)
 {
     const int64_t n = count * P.handles[0]->cells;
@@ -2425,13 +2425,15 @@ std::vector<TuneChoice> scan_choices(int maxnx, int maxn, bool fp64, bool dd, in
 }
 
 // Whether a solve whose sweep kernel the caller leaves open takes the row-scan sweep, and in which
-// shape: a rule, not a measurement, so a problem always sums in the same order.  The lines come from
-// step times (sweep and combine) of 240 shapes, 32^2 to 1024^2 cells and 8 to 8192 ordinates in all:
+// shape: a rule, not a measurement, so equal calls that it serves sum in the same order (the same problem
+// in another batch may take another shape, and where the rule leaves the choice open a measurement makes it).
+// The lines come from step times (sweep and combine) against the other kernels of some 1500 shapes, 8^2
+// to 1024^2 cells and 4 to 16384 ordinates in all:
 //   * media whose sigma_t changes in more than a quarter of the rows rebuild the multipliers too
-//     often, and the row-lane kernel is faster (random sigma_t: 256^2, 100 ordinates 74 us against 87, 64^2 25
-//     against 33, 24 x 200 41 against 80).  FP32 up to 128 columns, where a row has less to gain: more than a
+//     often, and the row-lane kernel is faster (random sigma_t: 256^2, 100 ordinates 74 us against 87, 64^2 22
+//     against 28, 24 x 200 41 against 64).  FP32 up to 128 columns, where a row has less to gain: more than a
 //     fifth (every fourth row, 32 x 60, 16 ordinates 19 against 22, 100 ordinates 24 / 22), but not for 32
-//     such rows or fewer a problem, where it is 3 us at most (40 x 28, 48 ordinates 17.5 / 20.5; 60 x 20
+//     such rows or fewer a problem, where there is little in it (40 x 28, 48 ordinates 17.5 / 18.0; 60 x 20
 //     18.9 / 17.6).  FP64 up to 64 columns, where a rebuild is short: 0.3 us per row and 8 in all against 0.25
 //     per row and column and 5 (64^2 33 / 27, 32^2 23 / 18, but 24 x 200 59 / 62, 8 x 64 22 / 27);
 //   * up to 512 columns it beat the row-lane kernel on every other shape (64^2 x 256: 22 us against

@@ -123,7 +123,7 @@ __host__ __device__ inline ScanShape scan_class_shape(int cls)
 
 // Values from one plane to the next of the row-scan sweep's partial fluxes and, for dense kernels, of its
 // ordinates: 32 times an odd number, so vector loads of every plane are aligned, and planes of 2^k cells
-// do not all start on the same memory channel (256^2 x 1024 dense: sweep 84 -> 79 us).
+// do not all start on the same memory channel (256^2 x 1024 dense: sweep 84 us -> 78).
 __host__ __device__ inline int64_t ang_plane(int64_t cells) { return ((cells + 31) / 32 | 1) * 32; }
 
 struct ScanTaskDev {

@@ -355,7 +355,7 @@ __global__ __launch_bounds__(64 * NW) void combine_vec_kernel(CombineArgs A)
 // The same for evenly spaced planes (the row-scan sweep's): a block's addresses come from one descriptor
 // and arithmetic instead of the chain block, system, problem, slot list, each a trip to memory, which is
 // most of what a small combine waits for; the state of a lone system is that of the solve.  256^2, 256
-// planes: 35 us -> 26; FP64 96 x 80, 36 planes: 11.4 -> 8.7; 301 x 517, 100 planes: 38 (cell by cell,
+// planes: 35 us -> 26; FP64 96 x 80, 36 planes: 11.4 -> 8.7; 301 x 517, 36 planes: 38 (cell by cell,
 // combine_many_kernel) -> 25 by vectors -> 22.  What is left is the sweep's tail in other XCDs' caches
 // and three trips of the maxima, the count and the finalize step.
 template <typename T, int NW>

@@ -345,7 +345,6 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* scalar_ptr
     return (const __attribute__((address_space(4))) T*)p;
 }
 
-
 // Everything one task needs (uniform values).
 template <typename T>
 struct ScanTask {

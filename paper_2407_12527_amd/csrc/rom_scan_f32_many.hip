@@ -5,7 +5,8 @@
 namespace rom {
 
 // The shape of each task follows its problem's width (scan_class).  One kernel holds every shape, so
-// a batch of uneven problems is one launch; 128 VGPRs, no spill.
+// a batch of uneven problems is one launch; 128 VGPRs, the values of a few (up to six, with inflow
+// tables 39) kept in scratch memory, in the widest shapes.
 template <int W, bool INF>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) void scan_many_kernel(ScanArgs A)
 {

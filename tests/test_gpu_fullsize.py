@@ -1,5 +1,6 @@
-"""Parity at the full workload sizes, in the launch configuration the bench times (strip sweep,
-the tile and band the bench pins), element by element against the FP64 oracle:
+"""Parity at the full workload sizes, in launch shapes of the strip sweep named here (the default
+paths, which take the row-scan sweep, are in test_gpu_default_paths.py), element by element against
+the FP64 oracle:
 
 * c3 (512 x 512, 64 samples of 128 stratified ordinates): every one of the 64 per-sample fluxes
   and the ensemble's FP64 mean and variance against the oracle's ensemble over the same

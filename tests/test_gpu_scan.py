@@ -177,8 +177,7 @@ def test_the_rule_repeats_itself(R):
 
 # Dense kernels: a source plane per ordinate, the angular flux in planes of four (BF16) or one (FP64), the
 # contraction on those planes.  Widths at the edges of the shapes, cell counts that end inside a
-# 16-byte store and a 128-byte line, ordinates that leave part of a plane and of a K step; 300 ordinates
-# run past one 256-wide tile.  A caller's unsymmetric kernel pins the contraction's orientation.  The
+# 16-byte store and a 128-byte line, ordinates that leave part of a plane and of a K step.  A caller's unsymmetric kernel pins the contraction's orientation.  The
 # bars of the other dense-kernel tests: 2e-3 with the BF16 contraction, 1e-11 in FP64.
 @pytest.mark.parametrize("nx,ny,n,kind,inflow", [
     (1, 1, 1, "hg", False), (3, 5, 7, "dense", True), (63, 9, 33, "hg", True), (64, 31, 12, "dense", False),
