@@ -57,11 +57,10 @@ HBM_PEAK_GBS = 8000.0
 BYTES_PER_ISO_UPDATE = 20.0 / 64.0
 BYTES_PER_ANG_UPDATE = 6.0
 
-# The sweep shape each workload's headline is timed with: left open.  librom then takes the row-scan
-# sweep by a rule on sizes and media, without a measurement, so the timed work is the same in every
-# process.  Step times on MI355X against the fastest shape of the other kernels: c1 0.235 / 0.457 ms,
-# c2 0.480 / 0.665, c3 3.88 / 7.13, c4 3.05 / 5.52, c5 38.2 / 55.5.
-PINNED = {w: {"sweep": "auto", "tile": "0x0", "band": 0, "diag_rows": 0, "diag_k": 0} for w in ("c1", "c2", "c3", "c4", "c5")}
+# The headline leaves the sweep to librom, which takes the row-scan sweep on every workload by a rule on
+# sizes and media, without a measurement, so the timed work is the same in every process.  Step times on
+# MI355X against the fastest shape of the other kernels: c1 0.230 / 0.457 ms, c2 0.480 / 0.665,
+# c3 3.87 / 7.13, c4 3.03 / 5.52, c5 39.9 / 55.5.
 
 # HBM bytes per sweep launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs (scaled by a 256 MiB copy:
 # 1 FETCH_SIZE KiB = 2 KiB read, 1 WRITE_SIZE KiB = 1 KiB written), for the row-scan sweep of each
@@ -85,11 +84,11 @@ MEASURED_TRAFFIC = {  # workload: [(kernel family, shape as in config, source ha
 }
 
 SCAN_TRAFFIC = {
-    "c1": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "9a8730968022d677", 690000)],
-    "c2": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "9a8730968022d677", 19530000)],
-    "c3": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 2, "waves_per_group": 16}, "9a8730968022d677", 543060000)],
-    "c4": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "9a8730968022d677", 478570000)],
-    "c5": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 2, "waves_per_group": 16}, "9a8730968022d677", 2504680000)],
+    "c1": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "328ce5c222d4673b", 740000)],
+    "c2": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "328ce5c222d4673b", 19580000)],
+    "c3": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 2, "waves_per_group": 16}, "328ce5c222d4673b", 538860000)],
+    "c4": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 1, "waves_per_group": 4}, "328ce5c222d4673b", 453830000)],
+    "c5": [("row-scan", {"lanes_per_group": 64, "ordinates_per_group": 2, "waves_per_group": 16}, "328ce5c222d4673b", 2223270000)],
 }
 
 
@@ -117,7 +116,7 @@ DESCR = {
     "c3": "c3: 512x512, ensemble of 64 samples x 128 stratified random ordinates, FP32, tol 1e-6, FP64 mean/var",
     "c4": "c4: 256x256, HG g=0.8, 1024 stratified random ordinates, FP32 sweeps + BF16 MFMA contraction, tol 1e-6",
     "c5": "c5: 200 independent problems, sides in {64..1024}, n = 4m with m in 4..128, random 8x8 block maps, FP32, "
-          "tol 1e-6, one persistent sweep launch per iteration",
+          "tol 1e-6, one sweep launch per iteration",
 }
 
 
@@ -129,20 +128,20 @@ def parse(argv=None):
     ap.add_argument("--workload", default="c5", choices=sorted(DESCR))
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
     ap.add_argument("--no-tte", action="store_true", help="skip the time-to-error measurement")
-    ap.add_argument("--autotune", action="store_true", help="let the autotuner pick the sweep shape")
-    ap.add_argument("--tile", default=None, help="sweep chunk x strip size, e.g. 8x4 (default: pinned)")
-    ap.add_argument("--band", type=int, default=None,
-                    help="strips (strip sweep) or row blocks (row-lane sweep) per workgroup (default: pinned)")
-    ap.add_argument("--sweep", default=None, choices=["auto", "strip", "diag"], help="sweep kernel (default: pinned)")
+    ap.add_argument("--autotune", action="store_true", help="the default: librom picks the sweep and its shape")
+    ap.add_argument("--tile", default=None, help="sweep chunk x strip size, e.g. 8x4")
+    ap.add_argument("--band", type=int, default=None, help="strips (strip sweep) or row blocks (row-lane sweep) per workgroup")
+    ap.add_argument("--sweep", default=None, choices=["auto", "strip", "diag"], help="sweep kernel")
     ap.add_argument("--diag-rows", type=int, default=None, help="row-lane sweep: rows per lane block (16, 64)")
     ap.add_argument("--diag-k", type=int, default=None, help="row-lane sweep: ordinates per lane (1, 2, 4)")
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="BYTES",
                     help="only run a device-to-device copy of BYTES (reference for HBM byte counters)")
     a = ap.parse_args(argv)
-    pin = {"sweep": "auto", "tile": "0x0", "band": 0, "diag_rows": 0, "diag_k": 0} if a.autotune else PINNED[a.workload]
-    for k in ("sweep", "tile", "band", "diag_rows", "diag_k"):
+    default = {"sweep": "auto", "tile": "0x0", "band": 0, "diag_rows": 0, "diag_k": 0}
+    a.shape_given = any(getattr(a, k) is not None for k in default)
+    for k, v in default.items():
         if getattr(a, k) is None:
-            setattr(a, k, pin[k])
+            setattr(a, k, v)
     if a.steps <= 0:
         a.steps = {"c1": 200, "c2": 200, "c3": 40, "c4": 20, "c5": 40}[a.workload]
     return a
@@ -406,7 +405,7 @@ def main():
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
 
-    config.update({"si_iterations": iters, **sweep_shape(shape), "shape_pinned": not a.autotune})
+    config.update({"si_iterations": iters, **sweep_shape(shape), "shape_pinned": a.shape_given})
     copy_gbs = copy_bandwidth(torch)
     roof = None
     if tot_sweeps > 0:
